@@ -273,14 +273,33 @@ __device__ __forceinline__ int wave_id() {
     return __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
 }
 
+// n / d for 0 <= n < 2^31 by a multiplication (d = 1 .. 2^31 - 1 fixed on the
+// host): mul = floor(2^(31 + l) / d) + 1 with l = ceil(log2 d), so that n * mul
+// exceeds n * 2^(31 + l) / d by at most n < 2^(31 + l) / d.  A division by a
+// kernel argument costs some 25 dependent instructions ahead of the first load.
+struct Div {
+    unsigned mul;
+    int shift;
+    __device__ __forceinline__ int operator()(int n) const {
+        return (int)(((unsigned long long)(unsigned)n * mul) >> shift);
+    }
+};
+inline Div make_div(int d) {
+    int l = 0;
+    while (l < 31 && (1ll << l) < d) ++l;
+    return Div{(unsigned)((1ull << (31 + l)) / (unsigned)d + 1), 31 + l};
+}
+
 // Merge softmax state (mb, lb, ab) into (m, l, a); m in the base-2 domain.
+// The fused multiply-adds are written out, so that every decomposition rounds
+// the same product.
 __device__ __forceinline__ void merge_state(float &m, float &l, float &a, float mb, float lb, float ab) {
     const float mx = fmaxf(m, mb);
     const float ms = (mx == -INFINITY) ? 0.f : mx;
     const float fa = __builtin_amdgcn_exp2f(m - ms);
     const float fb = __builtin_amdgcn_exp2f(mb - ms);
-    l = l * fa + lb * fb;
-    a = a * fa + ab * fb;
+    l = fmaf(lb, fb, l * fa);
+    a = fmaf(ab, fb, a * fa);
     m = mx;
 }
 
@@ -303,33 +322,21 @@ __device__ __forceinline__ void store_out(void *out, size_t idx, float v) {
 // current call's tag (about 10 ms at most; not reached in practice).
 constexpr int kMaxSpins = 1 << 14;
 
+// Rows of a generated-token tile read through an ancestry table: the row of
+// load u comes from the block of beam `beam[u]` of the source (already in
+// [0, k)).  The K/V pointers then address the source's beam-0 block, and
+// `stride` is the distance in bytes between the blocks of two beams (H * T *
+// row bytes).
+struct Anc {
+    int beam[kIt];
+    int k, stride;
+};
+
 // State of one wave tile: keys [t0, min(t0 + kTile, j1)) of one K/V stream
 // (t0 < j1), attended by the KB queries qr.  Kb/Vb point at row 0 of the
 // stream (rows of kLpr 16-byte slices).  On return m[i], l[i] (base-2 max and
 // sum of exp2) are wave-uniform and acc[i][e] holds, in every lane, the
 // unnormalised output for dims sub*kEpl + e.  prow is this wave's LDS area.
-// Rows of a generated-token tile read through an ancestry table: row j of
-// the hypothesis is row j of the block of beam row[j] of its source (an entry
-// outside [0, k) reads the hypothesis' own block, `self`).  The K/V pointers
-// then address the source's beam-0 block, and `stride` is the distance in
-// bytes between the blocks of two beams (H * T * row bytes).
-struct Anc {
-    const int32_t *row;
-    int self, k, stride;
-    // beams of this lane's rows of the first tile (t0 = 0), when `early`:
-    // loaded before the tile, so that its K/V loads need not wait for them
-    int first[kIt];
-    bool early;
-    __device__ __forceinline__ int beam(int j) const {
-        const int a = row[j];
-        return (a >= 0 && a < k) ? a : self;
-    }
-    // the beam of row j = t0 + u * rows-per-load + lane group, clamped to j1 - 1
-    __device__ __forceinline__ int beam_at(int t0, int u, int j) const {
-        return (early && t0 == 0) ? first[u] : beam(j);
-    }
-};
-
 template <int D, bool BF16, int KB, bool IND = false>
 __device__ __forceinline__ void tile_attend(const uint4 (&qr)[KB], const uint4 *__restrict__ Kb,
                                             const uint4 *__restrict__ Vb, int t0, int j1, int sub,
@@ -346,7 +353,7 @@ __device__ __forceinline__ void tile_attend(const uint4 (&qr)[KB], const uint4 *
     for (int u = 0; u < kIt; ++u) {
         const int j = min(t0 + u * kRpi + grp, j1 - 1);
         size_t at = (size_t)j * kLpr + sub;
-        if constexpr (IND) at += (size_t)an.beam_at(t0, u, j) * (an.stride / 16);
+        if constexpr (IND) at += (size_t)an.beam[u] * (an.stride / 16);
         kr[u] = load_nt(Kb + at);
         vr[u] = load_nt(Vb + at);
     }
@@ -490,8 +497,8 @@ struct ValuTile {
         tile_attend<D, BF16, KB, IND>(q.r, Kb, Vb, t0, j1, lane % kLpr, lane / kLpr, static_cast<float *>(lds),
                                       scale_log2, s.m, s.l, s.acc, an);
     }
-    // this wave's state into LDS: m_w[KB], l_w[KB], a_w[KB][D]
-    static __device__ __forceinline__ void to_lds(const St &s, int lane, float *m_w, float *l_w, float *a_w) {
+    // this wave's state into LDS: m_w and l_w (beam i at i * ms), a_w[KB][kAStride]
+    static __device__ __forceinline__ void to_lds(const St &s, int lane, float *m_w, float *l_w, int ms, float *a_w) {
         if (lane < kLpr) {
 #pragma unroll
             for (int i = 0; i < KB; ++i) {
@@ -502,8 +509,8 @@ struct ValuTile {
         if (lane == 0) {
 #pragma unroll
             for (int i = 0; i < KB; ++i) {
-                m_w[i] = s.m[i];
-                l_w[i] = s.l[i];
+                m_w[i * ms] = s.m[i];
+                l_w[i * ms] = s.l[i];
             }
         }
     }
@@ -638,8 +645,7 @@ struct MfmaTile {
 #pragma unroll
             for (int u = 0; u < kIt; ++u) {
                 const int j = t0 + grp + u * kRpi;
-                const int a = an.beam_at(t0, u, min(j, j1 - 1));
-                off[u] = j < j1 ? a * an.stride + (j * kLpr + sub) * 16 : 0x7ffffff0;
+                off[u] = j < j1 ? an.beam[u] * an.stride + (j * kLpr + sub) * 16 : 0x7ffffff0;
             }
 #pragma unroll
             for (int u = 0; u < kIt; ++u) kr[u] = load_rows(kres, off[u], 0);
@@ -730,15 +736,15 @@ struct MfmaTile {
 #pragma unroll
         for (int mb = 0; mb < NU; ++mb) st.acc[mb] = o[mb];
     }
-    static __device__ __forceinline__ void to_lds(const St &s, int lane, float *m_w, float *l_w, float *a_w) {
+    static __device__ __forceinline__ void to_lds(const St &s, int lane, float *m_w, float *l_w, int ms, float *a_w) {
         const int n = lane & 15, g = lane >> 4;
         if (n < KB) {
 #pragma unroll
             for (int mb = 0; mb < NU; ++mb)
                 *reinterpret_cast<f32x4_t *>(a_w + n * kAStride + 16 * mb + 4 * g) = s.acc[mb];
             if (g == 0) {
-                m_w[n] = s.m;
-                l_w[n] = s.l;
+                m_w[n * ms] = s.m;
+                l_w[n * ms] = s.l;
             }
         }
     }
@@ -747,17 +753,61 @@ struct MfmaTile {
 template <int D, bool BF16, int KB>
 using Tile = typename std::conditional<(BF16 && D >= 32), MfmaTile<D, KB>, ValuTile<D, BF16, KB>>::type;
 
+// Tile policy of a generated-token tile that belongs to one beam.  The matrix
+// cores take the beam as one of the KB columns at no extra cost (only its
+// column is used); the VALU tile attends it alone.
+template <int D, bool BF16, int KB>
+using OwnTile = typename std::conditional<(BF16 && D >= 32), MfmaTile<D, KB>, ValuTile<D, BF16, 1>>::type;
+
 // LDS area of one wave: large enough for a tile of KB beams or of one beam,
-// for the wave's acc (KB rows of kAStride floats) once its tile is done, and for one generated-
-// token tile state (m, l, acc[D] at float 4); a 16-byte multiple.
+// and for the wave's acc (KB rows of kAStride floats) once its tile is done;
+// a 16-byte multiple.
 template <int D, bool BF16, int KB>
 struct WaveLds {
-    static constexpr int a = Tile<D, BF16, KB>::kLdsBytes, b = Tile<D, BF16, 1>::kLdsBytes;
-    static constexpr int s = Tile<D, BF16, KB>::kAStride;
-    static constexpr int c = KB * s * 4 > (D + 4) * 4 ? KB * s * 4 : (D + 4) * 4;
+    static constexpr int a = Tile<D, BF16, KB>::kLdsBytes, b = OwnTile<D, BF16, KB>::kLdsBytes;
+    static constexpr int c = KB * Tile<D, BF16, KB>::kAStride * 4;
     static constexpr int kBytes = ((a > b ? (a > c ? a : c) : (b > c ? b : c)) + 15) / 16 * 16;
 };
 
+// What the kWaves waves from w0 on left in LDS for output (beam i, dim d):
+// their tiles' maxima and sums (beam-major, so one 16-byte read each) and
+// accumulators.
+struct TileStates {
+    float m[kWaves], l[kWaves], a[kWaves];
+};
+template <int AS, class L>
+__device__ __forceinline__ void load_states(L &lds, int w0, int i, int d, TileStates &s)
+{
+    static_assert(kWaves == 4, "four waves' maxima and sums in one read");
+    const f32x4_t m = *reinterpret_cast<const f32x4_t *>(&lds.m[i][w0]);
+    const f32x4_t l = *reinterpret_cast<const f32x4_t *>(&lds.l[i][w0]);
+#pragma unroll
+    for (int ww = 0; ww < kWaves; ++ww) {
+        s.m[ww] = m[ww];
+        s.l[ww] = l[ww];
+        s.a[ww] = lds.acc(w0 + ww)[i * AS + d];
+    }
+}
+
+// State of one chunk: its n tile states (the first n of s; the others, stale
+// or of other tiles, are masked) scaled to their common maximum and added in
+// key order.  Independent exponentials, where folding the tiles one by one
+// into the row's state is a chain of them.
+__device__ __forceinline__ void chunk_state(const TileStates &s, int n, float &m, float &l, float &a)
+{
+    m = -INFINITY;
+#pragma unroll
+    for (int ww = 0; ww < kWaves; ++ww) m = fmaxf(m, ww < n ? s.m[ww] : -INFINITY);
+    const float ms = (m == -INFINITY) ? 0.f : m;
+    l = 0.f;
+    a = 0.f;
+#pragma unroll
+    for (int ww = 0; ww < kWaves; ++ww) {
+        const float f = __builtin_amdgcn_exp2f((ww < n ? s.m[ww] : -INFINITY) - ms);
+        l = fmaf(ww < n ? s.l[ww] : 0.f, f, l);
+        a = fmaf(ww < n ? s.a[ww] : 0.f, f, a);
+    }
+}
 
 // Merger for (b, h) = bh: merges the chunk records of a source with more
 // than one chunk, in chunk order, and writes the normalised output.
@@ -771,24 +821,24 @@ struct WaveLds {
 // and the output becomes NaN if it never does (a loud failure instead of a
 // silent wrong merge or an endless wait).
 //
-// The records are the row's tile states, one per tile of keys in key order
-// (record slot j holds tile j), folded one by one from the empty state.
-// With a generated-token segment (SPLIT), record slot NT of (b, h) holds the
-// per-beam state of that segment; it is merged after the prefix tiles, and
-// the merger also writes the rows whose prefix has at most one chunk.
+// The records are the row's chunk states, in key order (record slot c holds
+// chunk c), folded one by one from the empty state.  With a generated-token
+// segment (SPLIT), record slot NT of (b, h) holds the per-beam state of that
+// segment; it is merged after the prefix chunks, and the merger also writes
+// the rows whose prefix has at most one chunk.
 template <int D, bool BF16, int KB, bool SPLIT>
 __device__ __forceinline__ void merge_chunks(const unsigned long long *__restrict__ part,
                                              const int32_t *__restrict__ src_len, void *__restrict__ out,
-                                             int bh, int n_bh, int H, int S, int NT, int t,
+                                             int bh, int n_bh, int H, Div by_H, int S, int NT, int t,
                                              unsigned long long epoch, unsigned long long *__restrict__ ctr)
 {
     using G = Geo<D, BF16>;
     if (bh >= n_bh) return;
-    const int b = bh / H;
+    const int b = by_H(bh);
     const int h = bh - b * H;
     const int L = min(max(src_len[b], 0), S);
-    if (!SPLIT && (L + G::kChunk - 1) / G::kChunk <= 1) return;  // written by the chunk workgroup itself
-    const int nc = (L + G::kTile - 1) / G::kTile;             // tile records of the prefix, in key order
+    const int nc = (L + G::kChunk - 1) / G::kChunk;           // chunk records of the prefix, in key order
+    if (!SPLIT && nc <= 1) return;                            // written by the chunk workgroup itself
     const int nrec = nc + (SPLIT && t > 0 ? 1 : 0);          // records to merge, in order
     constexpr int kRec = KB * (D + 2);
     unsigned long long c0 = 0;
@@ -846,119 +896,324 @@ __device__ __forceinline__ void merge_chunks(const unsigned long long *__restric
         __hip_atomic_store(ctr + bh, c0 + (any ? 2 : 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Softmax state of one hypothesis over its generated rows, in the compact
-// layout: m, l in every lane, lane l holding acc for dims l, l + 64, ...
-template <int D>
-struct GenState {
-    static constexpr int kE = (D + kWave - 1) / kWave;
-    float m, l, a[kE];
+// Generated rows of one (source, head) row: Kt/Vt [B*k, H, T, D], rows < t,
+// read directly or (anc != null) through the ancestry table.
+struct GenRows {
+    const uint4 *Kt, *Vt;
+    int T, t;
+    const int32_t *anc;
+    int ld;
 };
 
-// Softmax state of hypothesis `hyp` over its own generated rows [0, t) of
-// Kt/Vt for head h (t > 0): the tiles in order, each folded into the running
-// state.  Each tile's state passes through the wave's LDS area (m, l, then
-// acc[D] at float 4), so the running state takes a few registers per lane
-// rather than a whole tile state.
-template <int D, bool BF16, bool IND>
-__device__ __forceinline__ void generated_fold(const uint4 *__restrict__ q, const uint4 *__restrict__ Kb,
-                                               const uint4 *__restrict__ Vb, size_t hyp, int h, int H, int t,
-                                               int lane, void *lds, float scale_log2, GenState<D> &gs,
-                                               const Anc &an)
-{
-    using TL = Tile<D, BF16, 1>;
-    constexpr int kTile = Geo<D, BF16>::kTile, kE = GenState<D>::kE;
-    typename TL::Q qv;
-    TL::load_q(qv, q, hyp, h, H, lane);
-    float *slot = static_cast<float *>(lds);
-    gs.m = -INFINITY;
-    gs.l = 0.f;
+// LDS of a workgroup of KW waves that walks a row: each wave's tile area
+// (which then holds its acc for the fold), its (max, sum) per beam, and for
+// generated tiles the beam its task belongs to (-1: every beam) and, per tile
+// of a batch, whether the beams share it.
+template <int D, bool BF16, int KB, int KW>
+struct RowLds {
+    __attribute__((aligned(16))) float m[KB][KW], l[KB][KW];
+    __attribute__((aligned(16))) char t[KW][WaveLds<D, BF16, KB>::kBytes];
+    int task[KW];
+    unsigned char shared[kWave];
+    __device__ __forceinline__ float *acc(int w) { return reinterpret_cast<float *>(&t[w][0]); }
+};
+
+// Running softmax state of a thread's outputs x = tid + p * threads (beam
+// x / D, dim x % D).
+template <int N>
+struct OutState {
+    float m[N], l[N], a[N];
+    __device__ __forceinline__ void init() {
 #pragma unroll
-    for (int e = 0; e < kE; ++e) gs.a[e] = 0.f;
-    for (int t0 = 0; t0 < t; t0 += kTile) {
-        typename TL::St ts;
-        TL::template attend<IND>(qv, Kb, Vb, t0, t, lane, lds, scale_log2, ts, an);
-        TL::to_lds(ts, lane, slot, slot + 1, slot + 4);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // fold the tile into the running state (the order of merge_state)
-        const float tm = slot[0], tl = slot[1];
-        const float mx = fmaxf(gs.m, tm);
-        const float ms = (mx == -INFINITY) ? 0.f : mx;
-        const float fa = __builtin_amdgcn_exp2f(gs.m - ms);
-        const float fb = __builtin_amdgcn_exp2f(tm - ms);
-        gs.l = gs.l * fa + tl * fb;
-#pragma unroll
-        for (int e = 0; e < kE; ++e) {
-            const int d = lane + e * kWave;
-            if (d < D) gs.a[e] = gs.a[e] * fa + slot[4 + d] * fb;
+        for (int p = 0; p < N; ++p) {
+            m[p] = -INFINITY;
+            l[p] = 0.f;
+            a[p] = 0.f;
         }
-        gs.m = mx;
-        // the next tile's LDS writes stay behind these reads
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-}
+};
 
-// Beam `self` of a source, hypothesis hyp = source * k + self: its state over
-// its generated rows [0, t) of head h.  Without a table they are rows of its
-// own block of Kt/Vt; with an ancestry row (anc_row[j] = the beam whose block
-// holds its row j) each row comes from that beam's block.
-template <int D, bool BF16, bool ANC>
-__device__ __forceinline__ void generated_state(const uint4 *__restrict__ q, const uint4 *__restrict__ Kt,
-                                                const uint4 *__restrict__ Vt, size_t hyp, int h, int H, int T,
-                                                int t, int lane, void *lds, float scale_log2, GenState<D> &gs,
-                                                const int32_t *anc_row, int self, int k,
-                                                const int (&first)[kIt] = {}, bool early = false)
+// One (source, head) row walked by the KW waves of a workgroup in rounds of
+// KW tile tasks, one task per wave: the npt tiles of the prefix (Kbh/Vbh, L
+// keys), then with GEN the tiles of the generated tokens.  R receives the
+// prefix state (its chunks of kWaves tiles folded in key order), Gs the
+// generated tokens' state (tiles folded in key order), so the bits depend on
+// neither KW nor the rounds.
+//
+// A generated tile is one task per beam, over that beam's rows.  Through an
+// ancestry table (ANC), a tile whose rows have the same owner for every beam
+// -- beam search soon leaves one ancestor for all but the latest tokens -- is
+// one task for all of them, read once like a prefix tile.  The split cache
+// with 512 generated rows and 5 beams (512 rows of 75 to 300 prefix keys)
+// took 72 us when the first four waves walked each beam's tiles in turn; the
+// tasks spread over all waves take 23 us.
+//
+// The latest generated tile is one task per beam in any case (each beam's
+// last token is its own).  Its tasks go first, beside the first prefix tiles:
+// its rows lie in k separate blocks of memory, which a last round of a few
+// waves reads slowly (192 rows of up to 1024 prefix keys, 64 generated, k = 4:
+// 12.0 us, against 12.2 us with every generated tile after the prefix).
+template <int D, bool BF16, int KB, int KW, bool GEN, bool ANC>
+__device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typename Tile<D, BF16, KB>::Q &qv,
+                                         const uint4 *__restrict__ q, const uint4 *__restrict__ Kbh,
+                                         const uint4 *__restrict__ Vbh, int L, int b, int h, int H, const GenRows &gr,
+                                         float scale_log2, OutState<(KB * D + KW * kWave - 1) / (KW * kWave)> &R,
+                                         OutState<(KB * D + KW * kWave - 1) / (KW * kWave)> &Gs,
+                                         unsigned long long *trs)
 {
-    constexpr int kLpr = Geo<D, BF16>::kLpr;
-    if constexpr (ANC) {
-        const size_t base = ((hyp - self) * H + h) * (size_t)T * kLpr;   // the source's beam-0 block
-        Anc an{anc_row, self, k, H * T * kLpr * 16};
-        an.early = early;
+    using G = Geo<D, BF16>;
+    using TL = Tile<D, BF16, KB>;
+    using TO = OwnTile<D, BF16, KB>;
+    constexpr bool kOwnIsTile = std::is_same<TL, TO>::value;
+    constexpr int kTile = G::kTile, kLpr = G::kLpr, kRpi = G::kRpi;
+    constexpr int kThreads = KW * kWave, kPer = (KB * D + kThreads - 1) / kThreads;
+    constexpr int kBatch = kWave;   // generated tiles whose sharing one ballot holds
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = wave_id();
+    const int npt = (L + kTile - 1) / kTile;
+    const int ngt = GEN ? (gr.t + kTile - 1) / kTile : 0;
+    const size_t hyp0 = (size_t)b * KB;
+    float *const m_w = &lds.m[0][w], *const l_w = &lds.l[0][w];   // beam i at i * KW
+
+    R.init();
+    OutState<kPer> last;   // the early tasks' states, folded at the end
+    if constexpr (GEN) {
+        Gs.init();
+        last.init();
+    }
+
+    // owner of generated row j of beam i, in [0, KB)
+    auto owner = [&](int a, int i) { return (a >= 0 && a < KB) ? a : i; };
+
+    for (int gb = 0; gb == 0 || gb < ngt; gb += kBatch) {
+        const int npre = gb == 0 ? npt : 0;
+        const int ng = min(kBatch, ngt - gb);
+        // the tasks before the prefix: beams 0 .. early - 1 of the last tile
+        // (a multiple of kWaves, so that the prefix's chunks stay aligned)
+        const int early = GEN && ng > 0 && ngt <= kBatch ? KB / kWaves * kWaves : 0;
+        const int pre1 = early + npre;   // end of the prefix tasks
+        unsigned long long sh = 0;      // tiles of the batch with one owner per row for every beam
+        int ntask = npre + ng * KB;
+        // Does tile jt of the batch have one owner per row?  (one wave per tile)
+        auto mark_shared = [&]() {
+            for (int jt = w; jt < ng; jt += KW) {
+                bool same = KB == 1 || gb + jt < ngt - 1;
+                for (int p = lane; same && p < kTile; p += kWave) {
+                    const int j = (gb + jt) * kTile + p;   // < t: not the last tile
+                    const int32_t *col = gr.anc + hyp0 * gr.ld + j;
+                    int a[KB];
 #pragma unroll
-        for (int u = 0; u < kIt; ++u) an.first[u] = first[u];
-        generated_fold<D, BF16, true>(q, Kt + base, Vt + base, hyp, h, H, t, lane, lds, scale_log2, gs, an);
-    } else {
-        const size_t base = (hyp * H + h) * (size_t)T * kLpr;
-        generated_fold<D, BF16, false>(q, Kt + base, Vt + base, hyp, h, H, t, lane, lds, scale_log2, gs, Anc{});
+                    for (int i = 0; i < KB; ++i) a[i] = col[(size_t)i * gr.ld];
+#pragma unroll
+                    for (int i = 1; i < KB; ++i) same &= owner(a[i], i) == owner(a[0], 0);
+                }
+                const bool all = __builtin_amdgcn_ballot_w64(!same) == 0ull;
+                if (lane == 0) lds.shared[jt] = all;
+            }
+        };
+        auto read_shared = [&]() {
+            sh = __builtin_amdgcn_ballot_w64(lane < ng && lds.shared[lane] != 0);
+            ntask = npre + ng * KB - (int)__popcll(sh) * (KB - 1);
+        };
+        // This wave's position in the batch's generated tasks (tile by tile,
+        // in each the shared task or one per beam); advances with the rounds.
+        int cur_tile = 0, cur_first = pre1;
+        int g_tile = 0, g_beam = 0;
+        auto locate = [&](int task) {
+            if (task < early) {
+                g_tile = ng - 1;
+                g_beam = task;
+            } else if constexpr (ANC) {
+                for (;;) {
+                    const int c = (sh >> cur_tile) & 1ull ? 1 : KB;
+                    if (task < cur_first + c) break;
+                    cur_first += c;
+                    ++cur_tile;
+                }
+                g_tile = cur_tile;
+                g_beam = (sh >> cur_tile) & 1ull ? -1 : task - cur_first;
+            } else {
+                g_tile = (task - pre1) / KB;
+                g_beam = (task - pre1) - g_tile * KB;
+            }
+            if (task >= early && g_tile == ng - 1) g_beam += early;   // never shared (or KB == 1: early == 0)
+        };
+        // table entries of the rows of this wave's next generated task
+        int own[kIt];
+        auto load_owners = [&]() {
+            if constexpr (ANC) {
+                const int32_t *row = gr.anc + (hyp0 + max(g_beam, 0)) * gr.ld;
+#pragma unroll
+                for (int u = 0; u < kIt; ++u) own[u] = row[min((gb + g_tile) * kTile + u * kRpi + lane / kLpr, gr.t - 1)];
+            }
+        };
+        bool marked = !(ANC && ng > 0);
+        if constexpr (ANC) {
+            // when the first round needs no more than the early tasks and
+            // prefix tiles, the table is looked at after its loads have gone out
+            if (!marked && pre1 < KW) {
+                mark_shared();
+                __syncthreads();
+                read_shared();
+                marked = true;
+            }
+            if (w < early || (w >= pre1 && w < ntask)) {
+                locate(w);
+                load_owners();
+            }
+        }
+        for (int q0 = 0; q0 < ntask; q0 += KW) {
+            const int task = q0 + w;
+            if constexpr (GEN) {
+                if (task < early || (task >= pre1 && task < ntask)) {
+                    if constexpr (!ANC) locate(task);
+                    if (lane == 0) lds.task[w] = g_beam;
+                }
+            }
+            // One call site for the prefix tiles and, read directly on the
+            // matrix cores, the generated ones: half the instructions to fetch.
+            constexpr bool kJoin = GEN && !ANC && kOwnIsTile;
+            const bool gen = task < early || task >= pre1;
+            if (task < ntask && (kJoin || !gen)) {
+                const uint4 *Kw = Kbh, *Vw = Vbh;
+                int t0 = (task - early) * kTile, j1 = L;
+                if constexpr (kJoin) {
+                    if (gen) {
+                        const size_t base = ((hyp0 + g_beam) * H + h) * (size_t)gr.T * kLpr;
+                        Kw = gr.Kt + base;
+                        Vw = gr.Vt + base;
+                        t0 = (gb + g_tile) * kTile;
+                        j1 = gr.t;
+                    }
+                }
+                typename TL::St st;
+                TL::attend(qv, Kw, Vw, t0, j1, lane, &lds.t[w][0], scale_log2, st);
+                TL::to_lds(st, lane, m_w, l_w, KW, lds.acc(w));
+            }
+            if constexpr (GEN && !kJoin) {
+                if (task < ntask && gen) {
+                    const int t0 = (gb + g_tile) * kTile;
+                    if constexpr (ANC) {
+                        const size_t base = (hyp0 * H + h) * (size_t)gr.T * kLpr;   // the source's beam-0 block
+                        Anc an{{}, KB, H * gr.T * kLpr * 16};
+#pragma unroll
+                        for (int u = 0; u < kIt; ++u) an.beam[u] = owner(own[u], max(g_beam, 0));
+                        if (kOwnIsTile || g_beam < 0) {
+                            typename TL::St st;
+                            TL::template attend<true>(qv, gr.Kt + base, gr.Vt + base, t0, gr.t, lane, &lds.t[w][0],
+                                                      scale_log2, st, an);
+                            TL::to_lds(st, lane, m_w, l_w, KW, lds.acc(w));
+                        } else if constexpr (!kOwnIsTile) {
+                            typename TO::Q qo;
+                            typename TO::St st;
+                            TO::load_q(qo, q, hyp0 + g_beam, h, H, lane);
+                            TO::template attend<true>(qo, gr.Kt + base, gr.Vt + base, t0, gr.t, lane, &lds.t[w][0],
+                                                      scale_log2, st, an);
+                            TO::to_lds(st, lane, m_w + g_beam * KW, l_w + g_beam * KW, KW,
+                                       lds.acc(w) + g_beam * TL::kAStride);
+                        }
+                    } else {
+                        const size_t base = ((hyp0 + g_beam) * H + h) * (size_t)gr.T * kLpr;
+                        typename TO::Q qo;
+                        typename TO::St st;
+                        TO::load_q(qo, q, hyp0 + g_beam, h, H, lane);
+                        TO::attend(qo, gr.Kt + base, gr.Vt + base, t0, gr.t, lane, &lds.t[w][0], scale_log2, st);
+                        TO::to_lds(st, lane, m_w + g_beam * KW, l_w + g_beam * KW, KW,
+                                   lds.acc(w) + g_beam * TL::kAStride);
+                    }
+                }
+            }
+            bool fresh = false;
+            if constexpr (ANC) {
+                if (!marked) {
+                    mark_shared();
+                    marked = fresh = true;
+                }
+            }
+            __syncthreads();
+            if constexpr (ANC) {
+                if (fresh) read_shared();
+                const int next = task + KW;
+                if (next < ntask && (next < early || next >= pre1)) {
+                    locate(next);
+                    load_owners();   // in flight during the fold
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < kPer; ++p) {
+                const int x = tid + p * kThreads;
+                if (x < KB * D) {
+                    const int i = x / D, d = x - i * D;
+                    if constexpr (GEN) {
+                        const int we = i - q0;   // the wave of beam i's early task
+                        if (q0 < early && i < early && we >= 0 && we < KW) {
+                            last.m[p] = lds.m[i][we];
+                            last.l[p] = lds.l[i][we];
+                            last.a[p] = lds.acc(we)[i * TL::kAStride + d];
+                        }
+                    }
+#pragma unroll
+                    for (int g = 0; g < KW / kWaves; ++g) {
+                        const int n = pre1 - (q0 + g * kWaves);   // prefix tiles of this chunk, if any
+                        if (n > 0 && q0 + g * kWaves >= early) {
+                            TileStates ts;
+                            float cm, cl, ca;
+                            load_states<TL::kAStride>(lds, g * kWaves, i, d, ts);
+                            chunk_state(ts, n, cm, cl, ca);
+                            merge_state(R.m[p], R.l[p], R.a[p], cm, cl, ca);
+                        }
+                    }
+                    if constexpr (GEN) {
+                        // generated tiles, those of this beam, in order
+                        for (int ww = max(pre1 - q0, 0); ww < min(KW, ntask - q0); ++ww) {
+                            const int tb = __builtin_amdgcn_readfirstlane(lds.task[ww]);
+                            if (tb < 0 || tb == i)
+                                merge_state(Gs.m[p], Gs.l[p], Gs.a[p], lds.m[i][ww], lds.l[i][ww],
+                                            lds.acc(ww)[i * TL::kAStride + d]);
+                        }
+                    }
+                }
+            }
+            if (q0 + KW < ntask || gb + kBatch < ngt) __syncthreads();
+            if (gb == 0 && q0 == 0) trace::stamp(trs, 5);
+        }
+    }
+    if constexpr (GEN && KB >= kWaves) {
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) merge_state(Gs.m[p], Gs.l[p], Gs.a[p], last.m[p], last.l[p], last.a[p]);
     }
 }
 
-// Generated-token segment of (b, h) = bh (SPLIT only): wave w attends beam
-// i = w, w + 4, ... over that hypothesis' own rows [0, t) of Kt/Vt and stores
-// the beam's state in record slot NC of (b, h).
+// Generated-token segment of (b, h) = bh (SPLIT only): its state goes to
+// record slot NT of (b, h).
 template <int D, bool BF16, int KB, bool ANC>
-__device__ __forceinline__ void attend_generated(const uint4 *__restrict__ q, const uint4 *__restrict__ Kt,
-                                                 const uint4 *__restrict__ Vt, unsigned long long *__restrict__ part,
-                                                 int bh, int n_bh, int H, int NT, int T, int t,
-                                                 float scale_log2, unsigned long long epoch,
-                                                 const unsigned long long *__restrict__ ctr, void *lds,
-                                                 const int32_t *__restrict__ anc, int ld_anc)
+__device__ __forceinline__ void attend_generated(RowLds<D, BF16, KB, kWaves> &lds, const uint4 *__restrict__ q,
+                                                 unsigned long long *__restrict__ part, int bh, int n_bh, int H,
+                                                 Div by_H, int NT, const GenRows &gr, float scale_log2,
+                                                 unsigned long long epoch,
+                                                 const unsigned long long *__restrict__ ctr)
 {
-    if (bh >= n_bh || t <= 0) return;
-    const int b = bh / H;
+    using TL = Tile<D, BF16, KB>;
+    constexpr int kPer = (KB * D + kBlock - 1) / kBlock;
+    if (bh >= n_bh || gr.t <= 0) return;
+    const int b = by_H(bh);
     const int h = bh - b * H;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = wave_id();
     constexpr int kRec = KB * (D + 2);
     unsigned long long c0;
     const unsigned long long tag = call_tag(epoch, ctr + bh, c0);
+    typename TL::Q qv;
+    TL::load_q(qv, q, (size_t)b * KB, h, H, threadIdx.x & (kWave - 1));
+    OutState<kPer> R, Gs;
+    walk_row<D, BF16, KB, kWaves, true, ANC>(lds, qv, q, nullptr, nullptr, 0, b, h, H, gr, scale_log2, R, Gs, nullptr);
     unsigned long long *rec = part + ((size_t)bh * (NT + 1) + NT) * kRec;
-    for (int i = w; i < KB; i += kWaves) {
-        GenState<D> gs;
-        const size_t hyp = (size_t)b * KB + i;
-        generated_state<D, BF16, ANC>(q, Kt, Vt, hyp, h, H, T, t, lane, lds, scale_log2, gs,
-                                      ANC ? anc + hyp * ld_anc : nullptr, i, KB);
 #pragma unroll
-        for (int e = 0; e < GenState<D>::kE; ++e) {
-            const int d = lane + e * kWave;
-            if (d < D) store_word(rec + i * D + d, tag, gs.a[e]);
-        }
-        if (lane == 0) {
-            store_word(rec + KB * D + i, tag, gs.m);
-            store_word(rec + KB * D + KB + i, tag, gs.l);
+    for (int p = 0; p < kPer; ++p) {
+        const int x = threadIdx.x + p * kBlock;
+        if (x < KB * D) {
+            store_word(rec + x, tag, Gs.a[p]);
+            if (x % D == 0) {
+                store_word(rec + KB * D + x / D, tag, Gs.m[p]);
+                store_word(rec + KB * D + KB + x / D, tag, Gs.l[p]);
+            }
         }
     }
 }
@@ -966,9 +1221,9 @@ __device__ __forceinline__ void attend_generated(const uint4 *__restrict__ q, co
 template <int D, bool BF16, int KB, bool SPLIT, bool ANC = false>
 __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     const uint4 *__restrict__ q, const uint4 *__restrict__ K, const uint4 *__restrict__ V,
-    const int32_t *__restrict__ src_len, void *__restrict__ out,
-    unsigned long long *__restrict__ part,
-    int n_bh, int H, int S, int NC, float scale_log2, unsigned long long epoch,
+    const int32_t *__restrict__ src_len, int ng_blocks, int n_bh, int H, unsigned h_mul, int h_shift, int NC, int S,
+    float scale_log2, void *__restrict__ out,
+    unsigned long long *__restrict__ part, unsigned long long epoch,
     unsigned long long *__restrict__ ctr,
     const uint4 *__restrict__ Kt, const uint4 *__restrict__ Vt, int T, int t, const int32_t *__restrict__ anc,
     int ld_anc, NgramJob ngj)
@@ -978,17 +1233,15 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     constexpr int kLpr = G::kLpr;
     constexpr int kTile = G::kTile, kChunk = G::kChunk;
 
+    const Div by_H{h_mul, h_shift};
     // A fused decode step's n-gram rows take the first workgroups (a
     // multiple of 8, so the XCD residues of the ids below are kept).
-    if ((int)blockIdx.x < ngj.blocks) {
+    if ((int)blockIdx.x < ng_blocks) {
         ngram_job_block(ngj, blockIdx.x, kWaves);
         return;
     }
 
-    __shared__ float m_lds[kWaves][KB], l_lds[kWaves][KB];
-    // each wave's tile area, which then holds its acc[KB][D] for the merge
-    __shared__ __attribute__((aligned(16))) char t_lds[kWaves][WaveLds<D, BF16, KB>::kBytes];
-    auto a_lds = [&](int ww) { return reinterpret_cast<float *>(&t_lds[ww][0]); };
+    __shared__ RowLds<D, BF16, KB, kWaves> lds;
 
     // Workgroup g runs on XCD g % 8 (round-robin dispatch).  All chunks of
     // one (b, h), its generated-token workgroup and its merger get ids with
@@ -996,18 +1249,18 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     // generated-token workgroups (SPLIT only; each walks its tiles in
     // sequence, so they start first), the chunk workgroups, the mergers.
     const int n_bh8 = ((n_bh + kXcds - 1) / kXcds) * kXcds;
-    int g = blockIdx.x - ngj.blocks;
+    int g = blockIdx.x - ng_blocks;
     if constexpr (SPLIT) {
         if (g < n_bh8) {
-            attend_generated<D, BF16, KB, ANC>(q, Kt, Vt, part, g, n_bh, H, NC * kWaves, T, t, scale_log2, epoch,
-                                               ctr, &t_lds[wave_id()][0], anc, ld_anc);
+            attend_generated<D, BF16, KB, ANC>(lds, q, part, g, n_bh, H, by_H, NC * kWaves,
+                                               GenRows{Kt, Vt, T, t, anc, ld_anc}, scale_log2, epoch, ctr);
             return;
         }
         g -= n_bh8;
     }
     const int n_chunk_blocks = n_bh8 * NC;
     if (g >= n_chunk_blocks) {
-        merge_chunks<D, BF16, KB, SPLIT>(part, src_len, out, g - n_chunk_blocks, n_bh, H, S, NC * kWaves, t, epoch,
+        merge_chunks<D, BF16, KB, SPLIT>(part, src_len, out, g - n_chunk_blocks, n_bh, H, by_H, S, NC * kWaves, t, epoch,
                                          ctr);
         return;
     }
@@ -1016,7 +1269,7 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     const int bh = (slot / NC) * kXcds + xcd;
     const int c = slot - (slot / NC) * NC;
     if (bh >= n_bh) return;
-    const int b = bh / H;
+    const int b = by_H(bh);
     const int h = bh - b * H;
     const int L = min(max(src_len[b], 0), S);
     const int j0 = c * kChunk;
@@ -1043,206 +1296,95 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     const uint4 *Kbh = K + (size_t)bh * S * kLpr;
     const uint4 *Vbh = V + (size_t)bh * S * kLpr;
 
-    typename TL::St st;
-    TL::init(st);
     const int t0 = j0 + w * kTile;
-    if (t0 < j1) TL::attend(qv, Kbh, Vbh, t0, j1, lane, &t_lds[w][0], scale_log2, st);
-    TL::to_lds(st, lane, &m_lds[w][0], &l_lds[w][0], a_lds(w));
+    if (t0 < j1) {
+        typename TL::St st;
+        TL::attend(qv, Kbh, Vbh, t0, j1, lane, &lds.t[w][0], scale_log2, st);
+        TL::to_lds(st, lane, &lds.m[0][w], &lds.l[0][w], kWaves, lds.acc(w));
+    }
     __syncthreads();
 
-    if (!SPLIT && nc == 1) {
-        // the whole row: its tile states folded in key order from the empty state
-        for (int x = tid; x < KB * D; x += kBlock) {
-            const int i = x / D, d = x - i * D;
-            float mm = -INFINITY, ll = 0.f, aa = 0.f;
-#pragma unroll
-            for (int ww = 0; ww < kWaves; ++ww)
-                merge_state(mm, ll, aa, m_lds[ww][i], l_lds[ww][i], a_lds(ww)[i * TL::kAStride + d]);
-            store_out<BF16>(out, obase + (size_t)i * H * D + d, aa / ll);
-        }
-        return;
-    }
-
-    // One record per tile of the chunk (slot = tile index in the row):
+    // The chunk's state.  A whole row (one chunk) is folded from the empty
+    // state and finished here; otherwise it goes to record slot c of the row:
     // acc[KB][D], then m[KB], then l[KB].
-    const int NT = NC * kWaves;
     const int ntile = min(kWaves, (j1 - j0 + kTile - 1) / kTile);   // tiles of this chunk that hold keys
-    for (int ww = 0; ww < ntile; ++ww) {
-        unsigned long long *rec = part + ((size_t)bh * (NT + (SPLIT ? 1 : 0)) + c * kWaves + ww) * (KB * (D + 2));
-        for (int x = tid; x < KB * D; x += kBlock) {
-            const int i = x / D, d = x - i * D;
-            store_word(rec + x, tag, a_lds(ww)[i * TL::kAStride + d]);
+    unsigned long long *rec = part + ((size_t)bh * (NC * kWaves + (SPLIT ? 1 : 0)) + c) * (KB * (D + 2));
+    for (int x = tid; x < KB * D; x += kBlock) {
+        const int i = x / D, d = x - i * D;
+        float cm, cl, ca;
+        TileStates ts;
+        load_states<TL::kAStride>(lds, 0, i, d, ts);
+        chunk_state(ts, ntile, cm, cl, ca);
+        if (!SPLIT && nc == 1) {
+            float mm = -INFINITY, ll = 0.f, aa = 0.f;
+            merge_state(mm, ll, aa, cm, cl, ca);
+            store_out<BF16>(out, obase + (size_t)i * H * D + d, aa / ll);
+        } else {
+            store_word(rec + x, tag, ca);
             if (d == 0) {
-                store_word(rec + KB * D + i, tag, m_lds[ww][i]);
-                store_word(rec + KB * D + KB + i, tag, l_lds[ww][i]);
+                store_word(rec + KB * D + i, tag, cm);
+                store_word(rec + KB * D + KB + i, tag, cl);
             }
         }
     }
 }
 
-// One workgroup per (b, h) that walks all of its chunks itself: no partial
-// records, no merger, no cross-workgroup wait.  The row's jobs -- its chunks
-// and, for the split cache, the generated tokens -- are processed P at a
-// time by P groups of kWaves waves (workgroup of P*kBlock threads).  The
-// generated-token job goes first, so that its tiles are read alongside the
-// first chunks, but it is folded last.  The arithmetic and its order are
-// those of cross_attn_kernel -- each chunk's four wave states merged in wave
-// order, the chunk states folded in chunk order from the empty state, the
+// One workgroup per (b, h) that walks all of its tiles itself (walk_row): no
+// partial records, no merger, no cross-workgroup wait.  The arithmetic and
+// its order are those of cross_attn_kernel -- each chunk's tile states
+// combined, the chunk states folded in chunk order from the empty state, the
 // generated-token state last -- so both kernels give the same bits.  It pays
 // when there are enough (b, h) rows to fill the chip without splitting them.
 template <int D, bool BF16, int KB, bool SPLIT, int P, bool ANC = false>
 __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
     const uint4 *__restrict__ q, const uint4 *__restrict__ K, const uint4 *__restrict__ V,
-    const int32_t *__restrict__ src_len, void *__restrict__ out, int n_bh, int H, int S,
-    float scale_log2, const uint4 *__restrict__ Kt, const uint4 *__restrict__ Vt, int T, int t,
+    const int32_t *__restrict__ src_len, int ng_blocks, int H, unsigned h_mul, int h_shift, int S, float scale_log2,
+    void *__restrict__ out, const uint4 *__restrict__ Kt, const uint4 *__restrict__ Vt, int T, int t,
     const int32_t *__restrict__ anc, int ld_anc, NgramJob ngj)
 {
     using G = Geo<D, BF16>;
     using TL = Tile<D, BF16, KB>;
     constexpr int kLpr = G::kLpr;
-    constexpr int kTile = G::kTile, kChunk = G::kChunk;
     constexpr int kW = kWaves * P;                        // waves per workgroup
     constexpr int kThreads = kBlock * P;
     constexpr int kPer = (KB * D + kThreads - 1) / kThreads;  // outputs per thread
-    constexpr int kGB = SPLIT ? KB : 1, kGD = SPLIT ? D : 1;
 
-    __shared__ float m_lds[kW][KB], l_lds[kW][KB];
-    // each wave's tile area, which then holds its acc[KB][D] for the merge
-    __shared__ __attribute__((aligned(16))) char t_lds[kW][WaveLds<D, BF16, KB>::kBytes];
-    // generated-token states, kept until they are folded in at the end
-    __shared__ __attribute__((aligned(16))) float g_lds[kGB][kGD];
-    __shared__ float gm_lds[kGB], gl_lds[kGB];
+    __shared__ RowLds<D, BF16, KB, kW> lds;
 
+    const Div by_H{h_mul, h_shift};
     // A fused decode step's n-gram rows take the first workgroups.
-    if ((int)blockIdx.x < ngj.blocks) {
+    if ((int)blockIdx.x < ng_blocks) {
         ngram_job_block(ngj, blockIdx.x, kW);
         return;
     }
-    const int bh = blockIdx.x - ngj.blocks;
-    if (bh >= n_bh) return;
+    const int bh = blockIdx.x - ng_blocks;   // the grid holds no workgroup past the rows
     // trace words: 0 start, 1 end, 2 hardware ids, 3 row, 4 jobs, 5 first round folded
     unsigned long long *trs = trace_slot();
     trace::stamp(trs, 0);
-    const int b = bh / H;
+    const int b = by_H(bh);
     const int h = bh - b * H;
     const int L = min(max(src_len[b], 0), S);
-    const int nc = (L + kChunk - 1) / kChunk;
     const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int w = wave_id();
     const size_t obase = ((size_t)b * KB * H + h) * D;  // out[b, 0, h, 0]
-    // Through an ancestry table, the waves that take the generated-token job
-    // (first group, round 0) load the beams of their first tile's rows now,
-    // alongside src_len, instead of in front of the tile's K/V loads.
-    int first[kIt] = {};
-    bool early = false;
-    if constexpr (SPLIT && ANC) {
-        const int wg = wave_id();
-        if (t > 0 && wg < kWaves && wg < KB) {
-            const int32_t *row = anc + ((size_t)b * KB + wg) * ld_anc;
-            const int grp = (int)(threadIdx.x & (kWave - 1)) / kLpr;
-#pragma unroll
-            for (int u = 0; u < kIt; ++u) {
-                const int a = row[min(grp + u * G::kRpi, t - 1)];
-                first[u] = (a >= 0 && a < KB) ? a : wg;
-            }
-            early = true;
-        }
-    }
-
     typename TL::Q qv;
-    TL::load_q(qv, q, (size_t)b * KB, h, H, lane);
-    const uint4 *Kbh = K + (size_t)bh * S * kLpr;
-    const uint4 *Vbh = V + (size_t)bh * S * kLpr;
-
-    // running state of output x = tid + p * kThreads (beam x / D, dim x % D)
-    float Rm[kPer], Rl[kPer], Ra[kPer];
-#pragma unroll
-    for (int p = 0; p < kPer; ++p) {
-        Rm[p] = -INFINITY;
-        Rl[p] = 0.f;
-        Ra[p] = 0.f;
-    }
-
-    // jobs: [generated tokens (SPLIT, t > 0)] chunk 0, chunk 1, ...
-    const int ng = (SPLIT && t > 0) ? 1 : 0;
-    const int njobs = nc + ng;
-    const int cg = w / kWaves;   // group of this wave: job j0 + cg of each step
-    const int wt = w % kWaves;   // its wave in the group
-
-    // The first group takes the generated-token job (job 0 of round 0) here,
-    // before the job loop: its state stays out of the loop's registers (and
-    // beams loaded early from an ancestry table die before it).
+    TL::load_q(qv, q, (size_t)b * KB, h, H, tid & (kWave - 1));
+    OutState<kPer> R, Gs;
+    walk_row<D, BF16, KB, kW, SPLIT, ANC>(lds, qv, q, K + (size_t)bh * S * kLpr, V + (size_t)bh * S * kLpr, L, b, h, H,
+                                          GenRows{Kt, Vt, T, t, anc, ld_anc}, scale_log2, R, Gs, trs);
     if constexpr (SPLIT) {
-        if (ng && cg == 0) {
-            for (int i = wt; i < KB; i += kWaves) {
-                GenState<D> gs;
-                const size_t hyp = (size_t)b * KB + i;
-                generated_state<D, BF16, ANC>(q, Kt, Vt, hyp, h, H, T, t, lane, &t_lds[w][0], scale_log2, gs,
-                                              ANC ? anc + hyp * ld_anc : nullptr, i, KB, first, early && i == wt);
+        if (t > 0) {
 #pragma unroll
-                for (int e = 0; e < GenState<D>::kE; ++e) {
-                    const int d = lane + e * kWave;
-                    if (d < D) g_lds[i][d] = gs.a[e];
-                }
-                if (lane == 0) {
-                    gm_lds[i] = gs.m;
-                    gl_lds[i] = gs.l;
-                }
-            }
+            for (int p = 0; p < kPer; ++p) merge_state(R.m[p], R.l[p], R.a[p], Gs.m[p], Gs.l[p], Gs.a[p]);
         }
     }
-    for (int j0 = 0; j0 < njobs; j0 += P) {
-        const int c = j0 + cg - ng;  // chunk of this group's job; -1: generated tokens
-        if (j0 + cg < njobs && c < 0) {
-            // the generated-token job, already taken before this loop
-        } else if (j0 + cg < njobs) {
-            typename TL::St st;
-            TL::init(st);
-            const int j1 = min((c + 1) * kChunk, L);
-            const int t0 = c * kChunk + wt * kTile;
-            if (t0 < j1) TL::attend(qv, Kbh, Vbh, t0, j1, lane, &t_lds[w][0], scale_log2, st);
-            TL::to_lds(st, lane, &m_lds[w][0], &l_lds[w][0], reinterpret_cast<float *>(&t_lds[w][0]));
-        }
-        __syncthreads();
-#pragma unroll
-        for (int p = 0; p < kPer; ++p) {
-            const int x = tid + p * kThreads;
-            if (x < KB * D) {
-                const int i = x / D, d = x - i * D;
-                for (int g = 0; g < P && j0 + g < njobs; ++g) {
-                    if (j0 + g < ng) continue;  // the generated-token job is folded last
-                    // the chunk's tile states, in key order (a tile past the
-                    // row's end holds the empty state, which folds to nothing)
-#pragma unroll
-                    for (int ww = 0; ww < kWaves; ++ww) {
-                        const int w0 = g * kWaves + ww;
-                        const float *aw = reinterpret_cast<const float *>(&t_lds[w0][0]);
-                        merge_state(Rm[p], Rl[p], Ra[p], m_lds[w0][i], l_lds[w0][i], aw[i * TL::kAStride + d]);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (j0 == 0) trace::stamp(trs, 5);
-    }
-    if (ng) {
-#pragma unroll
-        for (int p = 0; p < kPer; ++p) {
-            const int x = tid + p * kThreads;
-            if (x < KB * D) {
-                const int i = x / D, d = x - i * D;
-                merge_state(Rm[p], Rl[p], Ra[p], gm_lds[i], gl_lds[i], g_lds[i][d]);
-            }
-        }
-    }
+    const int njobs = (L + G::kChunk - 1) / G::kChunk + (SPLIT && t > 0 ? 1 : 0);   // chunks, generated tokens
     const bool any = njobs > 0;
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
         const int x = tid + p * kThreads;
         if (x < KB * D) {
             const int i = x / D, d = x - i * D;
-            store_out<BF16>(out, obase + (size_t)i * H * D + d, any ? Ra[p] / Rl[p] : 0.f);  // no key: zero row
+            store_out<BF16>(out, obase + (size_t)i * H * D + d, any ? R.a[p] / R.l[p] : 0.f);  // no key: zero row
         }
     }
     trace::stamp(trs, 1);
@@ -1286,10 +1428,11 @@ hipError_t launch_split(const AttnArgs &a, int NC)
     ng.blocks = ng.rows > 0 ? (ng.rows + kWaves - 1) / kWaves : 0;
     ng.blocks = (ng.blocks + kXcds - 1) / kXcds * kXcds;
     const long long nblk = ng.blocks + (SPLIT ? n_bh8 : 0) + n_bh8 * NC + mergers;
+    const Div dv = make_div(a.H);
     hipLaunchKernelGGL((cross_attn_kernel<D, BF16, KB, SPLIT, ANC>), dim3((unsigned)nblk), dim3(kBlock), 0,
                        a.stream, static_cast<const uint4 *>(a.q), static_cast<const uint4 *>(a.K),
-                       static_cast<const uint4 *>(a.V), a.src_len, a.out, part, n_bh, a.H, a.S,
-                       NC, (float)scale_log2, a.epoch, ctr, static_cast<const uint4 *>(a.Kt),
+                       static_cast<const uint4 *>(a.V), a.src_len, ng.blocks, n_bh, a.H, dv.mul, dv.shift, NC, a.S,
+                       (float)scale_log2, a.out, part, a.epoch, ctr, static_cast<const uint4 *>(a.Kt),
                        static_cast<const uint4 *>(a.Vt), a.T, a.t, a.anc, a.ld_anc, ng);
     return hipGetLastError();
 }
@@ -1301,10 +1444,12 @@ hipError_t launch_whole(const AttnArgs &a)
     const double scale_log2 = 1.4426950408889634074 / sqrt((double)D);
     NgramJob ng = a.ng;
     ng.blocks = ng.rows > 0 ? (ng.rows + kWaves * P - 1) / (kWaves * P) : 0;
+    const Div dv = make_div(a.H);
     hipLaunchKernelGGL((attn_whole_kernel<D, BF16, KB, SPLIT, P, ANC>), dim3((unsigned)(ng.blocks + n_bh)),
                        dim3(kBlock * P), 0,
                        a.stream, static_cast<const uint4 *>(a.q), static_cast<const uint4 *>(a.K),
-                       static_cast<const uint4 *>(a.V), a.src_len, a.out, n_bh, a.H, a.S, (float)scale_log2,
+                       static_cast<const uint4 *>(a.V), a.src_len, ng.blocks, a.H, dv.mul, dv.shift, a.S,
+                       (float)scale_log2, a.out,
                        static_cast<const uint4 *>(a.Kt), static_cast<const uint4 *>(a.Vt), a.T, a.t, a.anc,
                        a.ld_anc, ng);
     return hipGetLastError();
