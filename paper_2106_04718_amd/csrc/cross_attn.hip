@@ -322,41 +322,67 @@ __device__ __forceinline__ void store_out(void *out, size_t idx, float v) {
 // current call's tag (about 10 ms at most; not reached in practice).
 constexpr int kMaxSpins = 1 << 14;
 
-// Rows of a generated-token tile read through an ancestry table: the row of
-// load u comes from the block of beam `beam[u]` of the source (already in
-// [0, k)).  The K/V pointers then address the source's beam-0 block, and
-// `stride` is the distance in bytes between the blocks of two beams (H * T *
-// row bytes).
-struct Anc {
-    int beam[kIt];
-    int k, stride;
+// One wave tile's K and V rows, in the coalesced layout: instruction u reads
+// rows t0 + u*kRpi + grp whole, kLpr lanes per row (loads of 16 half rows
+// each are markedly slower).
+struct Rows {
+    uint4 k[kIt], v[kIt];
 };
 
-// State of one wave tile: keys [t0, min(t0 + kTile, j1)) of one K/V stream
-// (t0 < j1), attended by the KB queries qr.  Kb/Vb point at row 0 of the
-// stream (rows of kLpr 16-byte slices).  On return m[i], l[i] (base-2 max and
+// Issues the loads of keys [t0, t0 + kTile) of a stream of j1 rows at Kb/Vb.
+// Buffer loads whose range ends at row j1: rows past it read as zero without
+// a memory access and are masked by the tile, and K and V share one offset
+// register.  All K first, so that the tile can start while V is in flight
+// (ORDER holds the compiler to it, where the loads and the tile are apart).
+template <int D, bool BF16, bool ORDER>
+__device__ __forceinline__ void load_tile(Rows &r, const uint4 *__restrict__ Kb, const uint4 *__restrict__ Vb, int t0,
+                                          int j1, int lane)
+{
+    using G = Geo<D, BF16>;
+    constexpr int kRow = D * Elem<BF16>::size;
+    const auto kres = row_rsrc(Kb, j1 * kRow), vres = row_rsrc(Vb, j1 * kRow);
+    const int off = (t0 + lane / G::kLpr) * kRow + lane % G::kLpr * 16;
+    if constexpr (ORDER) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kIt; ++u) r.k[u] = load_rows(kres, off, u * G::kRpi * kRow);
+    if constexpr (ORDER) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kIt; ++u) r.v[u] = load_rows(vres, off, u * G::kRpi * kRow);
+    if constexpr (ORDER) __builtin_amdgcn_sched_barrier(0);
+}
+
+// The same with an offset per row load and a range of `bytes`: the tiles of a
+// row read through an ancestry table.
+__device__ __forceinline__ void load_tile_at(Rows &r, const uint4 *__restrict__ Kb, const uint4 *__restrict__ Vb,
+                                             int bytes, const int (&off)[kIt])
+{
+    const auto kres = row_rsrc(Kb, bytes), vres = row_rsrc(Vb, bytes);
+#pragma unroll
+    for (int u = 0; u < kIt; ++u) r.k[u] = load_rows(kres, off[u], 0);
+#pragma unroll
+    for (int u = 0; u < kIt; ++u) r.v[u] = load_rows(vres, off[u], 0);
+}
+
+// Barrier of a workgroup for LDS only: this wave's global loads in flight are
+// not waited for (unlike __syncthreads).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// State of one wave tile: keys [t0, min(t0 + kTile, j1)), rows kr/vr (t0 <
+// j1), attended by the KB queries qr.  On return m[i], l[i] (base-2 max and
 // sum of exp2) are wave-uniform and acc[i][e] holds, in every lane, the
 // unnormalised output for dims sub*kEpl + e.  prow is this wave's LDS area.
-template <int D, bool BF16, int KB, bool IND = false>
-__device__ __forceinline__ void tile_attend(const uint4 (&qr)[KB], const uint4 *__restrict__ Kb,
-                                            const uint4 *__restrict__ Vb, int t0, int j1, int sub,
+template <int D, bool BF16, int KB>
+__device__ __forceinline__ void tile_attend(const uint4 (&qr)[KB], const uint4 (&kr)[kIt], const uint4 (&vr)[kIt],
+                                            int t0, int j1, int sub,
                                             int grp, float *prow, float scale_log2, float (&m)[KB],
-                                            float (&l)[KB], float (&acc)[KB][Geo<D, BF16>::kEpl],
-                                            const Anc &an = Anc{})
+                                            float (&l)[KB], float (&acc)[KB][Geo<D, BF16>::kEpl])
 {
     using G = Geo<D, BF16>;
     constexpr int kEpl = G::kEpl, kLpr = G::kLpr, kRpi = G::kRpi;
-    // Row loads: instruction u reads rows t0 + u*kRpi + grp.  Rows past j1
-    // re-read row j1 - 1 (valid data, never padding) and are masked.
-    uint4 kr[kIt], vr[kIt];
-#pragma unroll
-    for (int u = 0; u < kIt; ++u) {
-        const int j = min(t0 + u * kRpi + grp, j1 - 1);
-        size_t at = (size_t)j * kLpr + sub;
-        if constexpr (IND) at += (size_t)an.beam[u] * (an.stride / 16);
-        kr[u] = load_nt(Kb + at);
-        vr[u] = load_nt(Vb + at);
-    }
     // QK^T: partial dots of this lane's slice, then a reduce-scatter in the
     // row group, after which the lane owns whole score rows.
     float d[kIt][KB];
@@ -490,12 +516,10 @@ struct ValuTile {
             for (int e = 0; e < kEpl; ++e) s.acc[i][e] = 0.f;
         }
     }
-    template <bool IND = false>
-    static __device__ __forceinline__ void attend(const Q &q, const uint4 *__restrict__ Kb,
-                                                  const uint4 *__restrict__ Vb, int t0, int j1, int lane,
-                                                  void *lds, float scale_log2, St &s, const Anc &an = Anc{}) {
-        tile_attend<D, BF16, KB, IND>(q.r, Kb, Vb, t0, j1, lane % kLpr, lane / kLpr, static_cast<float *>(lds),
-                                      scale_log2, s.m, s.l, s.acc, an);
+    static __device__ __forceinline__ void attend(const Q &q, const Rows &r, int t0, int j1, int lane, void *lds,
+                                                  float scale_log2, St &s) {
+        tile_attend<D, BF16, KB>(q.r, r.k, r.v, t0, j1, lane % kLpr, lane / kLpr, static_cast<float *>(lds),
+                                 scale_log2, s.m, s.l, s.acc);
     }
     // this wave's state into LDS: m_w and l_w (beam i at i * ms), a_w[KB][kAStride]
     static __device__ __forceinline__ void to_lds(const St &s, int lane, float *m_w, float *l_w, int ms, float *a_w) {
@@ -616,47 +640,16 @@ struct MfmaTile {
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    template <bool IND = false>
-    static __device__ __forceinline__ void attend(const Q &q, const uint4 *__restrict__ Kb,
-                                                  const uint4 *__restrict__ Vb, int t0, int j1, int lane,
-                                                  void *lds, float scale_log2, St &st, const Anc &an = Anc{}) {
+    static __device__ __forceinline__ void attend(const Q &q, const Rows &rw, int t0, int j1, int lane, void *lds,
+                                                  float scale_log2, St &st) {
         const int n = lane & 15, g = lane >> 4;
-        // Row loads in the coalesced layout: kLpr lanes per row, so one
-        // instruction reads whole rows (loads of 16 half rows each are
-        // markedly slower).  Buffer loads whose range ends at row j1: rows
-        // past it read as zero without a memory access and are masked, and
-        // K and V share one offset register.  All K first, so its trip
-        // through LDS can start while V is in flight.
         constexpr int kRpi = kWave / kLpr;
         const int sub = lane % kLpr, grp = lane / kLpr;
-        uint4 kr[kIt], vr[kIt];
-        if constexpr (!IND) {
-            const auto kres = row_rsrc(Kb, j1 * 2 * D), vres = row_rsrc(Vb, j1 * 2 * D);
-            const int off = ((t0 + grp) * kLpr + sub) * 16;
-#pragma unroll
-            for (int u = 0; u < kIt; ++u) kr[u] = load_rows(kres, off, u * kRpi * 2 * D);
-#pragma unroll
-            for (int u = 0; u < kIt; ++u) vr[u] = load_rows(vres, off, u * kRpi * 2 * D);
-        } else {
-            // each row from its beam's block; rows at or past j1 get an
-            // offset past the range and read zero without a memory access
-            const auto kres = row_rsrc(Kb, an.k * an.stride), vres = row_rsrc(Vb, an.k * an.stride);
-            int off[kIt];
-#pragma unroll
-            for (int u = 0; u < kIt; ++u) {
-                const int j = t0 + grp + u * kRpi;
-                off[u] = j < j1 ? an.beam[u] * an.stride + (j * kLpr + sub) * 16 : 0x7ffffff0;
-            }
-#pragma unroll
-            for (int u = 0; u < kIt; ++u) kr[u] = load_rows(kres, off[u], 0);
-#pragma unroll
-            for (int u = 0; u < kIt; ++u) vr[u] = load_rows(vres, off[u], 0);
-        }
         // K through LDS into the MFMA A layout: lane l takes row 16 kb + n,
         // dims 32 s + 8 g .. + 8
         char *vt = static_cast<char *>(lds);
 #pragma unroll
-        for (int u = 0; u < kIt; ++u) *reinterpret_cast<uint4 *>(vt + lds_off(u * kRpi + grp, sub)) = kr[u];
+        for (int u = 0; u < kIt; ++u) *reinterpret_cast<uint4 *>(vt + lds_off(u * kRpi + grp, sub)) = rw.k[u];
         lds_fence();
         uint4 ka[NKB][NS];
 #pragma unroll
@@ -668,7 +661,7 @@ struct MfmaTile {
         // the V rows take the K rows' place (this wave's reads of K are done:
         // LDS instructions of one wave complete in order)
 #pragma unroll
-        for (int u = 0; u < kIt; ++u) *reinterpret_cast<uint4 *>(vt + lds_off(u * kRpi + grp, sub)) = vr[u];
+        for (int u = 0; u < kIt; ++u) *reinterpret_cast<uint4 *>(vt + lds_off(u * kRpi + grp, sub)) = rw.v[u];
         f32x4_t sc[NKB];
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
@@ -966,6 +959,10 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typ
     using TO = OwnTile<D, BF16, KB>;
     constexpr bool kOwnIsTile = std::is_same<TL, TO>::value;
     constexpr int kTile = G::kTile, kLpr = G::kLpr, kRpi = G::kRpi;
+    // Rows of the next round on their way during this round's fold.  Where the
+    // registers for it (124, four waves per SIMD) are there: with D = 128, the
+    // VALU tile or generated tokens it costs a wave per SIMD.
+    constexpr bool kAhead = BF16 && (D == 32 || D == 64) && !GEN;
     constexpr int kThreads = KW * kWave, kPer = (KB * D + kThreads - 1) / kThreads;
     constexpr int kBatch = kWave;   // generated tiles whose sharing one ballot holds
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = wave_id();
@@ -1037,13 +1034,54 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typ
             }
             if (task >= early && g_tile == ng - 1) g_beam += early;   // never shared (or KB == 1: early == 0)
         };
-        // table entries of the rows of this wave's next generated task
+        // This wave's task of a round: where its keys are, and its loads.  A
+        // task read through the table first needs the table entries of its
+        // rows (find), then its rows' loads go out (fetch).
+        Rows rows;
+        typename TO::Q qo;
         int own[kIt];
-        auto load_owners = [&]() {
+        int t0 = 0, j1 = 0;
+        bool gen = false;
+        auto find = [&](int task) {
+            gen = GEN && (task < early || task >= pre1);
+            t0 = (task - early) * kTile;
+            j1 = task < ntask ? L : 0;   // no task: loads of an empty range
+            if (!gen || task >= ntask) return;
+            locate(task);
+            t0 = (gb + g_tile) * kTile;
+            j1 = gr.t;
             if constexpr (ANC) {
                 const int32_t *row = gr.anc + (hyp0 + max(g_beam, 0)) * gr.ld;
 #pragma unroll
-                for (int u = 0; u < kIt; ++u) own[u] = row[min((gb + g_tile) * kTile + u * kRpi + lane / kLpr, gr.t - 1)];
+                for (int u = 0; u < kIt; ++u) own[u] = row[min(t0 + u * kRpi + lane / kLpr, gr.t - 1)];
+            }
+            if constexpr (!kOwnIsTile) {
+                if (g_beam >= 0) TO::load_q(qo, q, hyp0 + g_beam, h, H, lane);
+            }
+        };
+        auto fetch = [&]() {
+            constexpr int kRow = kLpr * 16;
+            const uint4 *Kw = Kbh, *Vw = Vbh;
+            if constexpr (GEN) {
+                if (gen) {
+                    // read through the table: from the source's beam-0 block on
+                    const size_t base = ((ANC ? hyp0 : hyp0 + g_beam) * H + h) * (size_t)gr.T * kLpr;
+                    Kw = gr.Kt + base;
+                    Vw = gr.Vt + base;
+                }
+            }
+            if constexpr (ANC) {
+                const int stride = gen ? H * gr.T * kRow : 0;   // bytes between two beams' blocks
+                int off[kIt];
+#pragma unroll
+                for (int u = 0; u < kIt; ++u) {
+                    const int j = t0 + u * kRpi + lane / kLpr;
+                    const int at = owner(own[u], max(g_beam, 0)) * stride + j * kRow + lane % kLpr * 16;
+                    off[u] = j < j1 ? at : 0x7ffffff0;   // past the range: zero, no access
+                }
+                load_tile_at(rows, Kw, Vw, gen ? KB * stride : j1 * kRow, off);
+            } else {
+                load_tile<D, BF16, kAhead>(rows, Kw, Vw, t0, j1, lane);
             }
         };
         bool marked = !(ANC && ng > 0);
@@ -1052,74 +1090,30 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typ
             // prefix tiles, the table is looked at after its loads have gone out
             if (!marked && pre1 < KW) {
                 mark_shared();
-                __syncthreads();
+                lds_barrier();
                 read_shared();
                 marked = true;
             }
-            if (w < early || (w >= pre1 && w < ntask)) {
-                locate(w);
-                load_owners();
-            }
         }
+        find(w);
+        if constexpr (kAhead) fetch();
         for (int q0 = 0; q0 < ntask; q0 += KW) {
             const int task = q0 + w;
-            if constexpr (GEN) {
-                if (task < early || (task >= pre1 && task < ntask)) {
-                    if constexpr (!ANC) locate(task);
-                    if (lane == 0) lds.task[w] = g_beam;
+            if (task < ntask) {
+                if constexpr (GEN) {
+                    if (gen && lane == 0) lds.task[w] = g_beam;
                 }
-            }
-            // One call site for the prefix tiles and, read directly on the
-            // matrix cores, the generated ones: half the instructions to fetch.
-            constexpr bool kJoin = GEN && !ANC && kOwnIsTile;
-            const bool gen = task < early || task >= pre1;
-            if (task < ntask && (kJoin || !gen)) {
-                const uint4 *Kw = Kbh, *Vw = Vbh;
-                int t0 = (task - early) * kTile, j1 = L;
-                if constexpr (kJoin) {
-                    if (gen) {
-                        const size_t base = ((hyp0 + g_beam) * H + h) * (size_t)gr.T * kLpr;
-                        Kw = gr.Kt + base;
-                        Vw = gr.Vt + base;
-                        t0 = (gb + g_tile) * kTile;
-                        j1 = gr.t;
-                    }
-                }
-                typename TL::St st;
-                TL::attend(qv, Kw, Vw, t0, j1, lane, &lds.t[w][0], scale_log2, st);
-                TL::to_lds(st, lane, m_w, l_w, KW, lds.acc(w));
-            }
-            if constexpr (GEN && !kJoin) {
-                if (task < ntask && gen) {
-                    const int t0 = (gb + g_tile) * kTile;
-                    if constexpr (ANC) {
-                        const size_t base = (hyp0 * H + h) * (size_t)gr.T * kLpr;   // the source's beam-0 block
-                        Anc an{{}, KB, H * gr.T * kLpr * 16};
-#pragma unroll
-                        for (int u = 0; u < kIt; ++u) an.beam[u] = owner(own[u], max(g_beam, 0));
-                        if (kOwnIsTile || g_beam < 0) {
-                            typename TL::St st;
-                            TL::template attend<true>(qv, gr.Kt + base, gr.Vt + base, t0, gr.t, lane, &lds.t[w][0],
-                                                      scale_log2, st, an);
-                            TL::to_lds(st, lane, m_w, l_w, KW, lds.acc(w));
-                        } else if constexpr (!kOwnIsTile) {
-                            typename TO::Q qo;
-                            typename TO::St st;
-                            TO::load_q(qo, q, hyp0 + g_beam, h, H, lane);
-                            TO::template attend<true>(qo, gr.Kt + base, gr.Vt + base, t0, gr.t, lane, &lds.t[w][0],
-                                                      scale_log2, st, an);
-                            TO::to_lds(st, lane, m_w + g_beam * KW, l_w + g_beam * KW, KW,
-                                       lds.acc(w) + g_beam * TL::kAStride);
-                        }
-                    } else {
-                        const size_t base = ((hyp0 + g_beam) * H + h) * (size_t)gr.T * kLpr;
-                        typename TO::Q qo;
-                        typename TO::St st;
-                        TO::load_q(qo, q, hyp0 + g_beam, h, H, lane);
-                        TO::attend(qo, gr.Kt + base, gr.Vt + base, t0, gr.t, lane, &lds.t[w][0], scale_log2, st);
-                        TO::to_lds(st, lane, m_w + g_beam * KW, l_w + g_beam * KW, KW,
-                                   lds.acc(w) + g_beam * TL::kAStride);
-                    }
+                // the loads beside their use: the VALU tile takes its V rows late
+                if (kOwnIsTile || !gen || g_beam < 0) {
+                    typename TL::St st;
+                    if constexpr (!kAhead) fetch();
+                    TL::attend(qv, rows, t0, j1, lane, &lds.t[w][0], scale_log2, st);
+                    TL::to_lds(st, lane, m_w, l_w, KW, lds.acc(w));
+                } else if constexpr (!kOwnIsTile) {
+                    typename TO::St st;
+                    fetch();
+                    TO::attend(qo, rows, t0, j1, lane, &lds.t[w][0], scale_log2, st);
+                    TO::to_lds(st, lane, m_w + g_beam * KW, l_w + g_beam * KW, KW, lds.acc(w) + g_beam * TL::kAStride);
                 }
             }
             bool fresh = false;
@@ -1129,14 +1123,15 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typ
                     marked = fresh = true;
                 }
             }
-            __syncthreads();
+            lds_barrier();
             if constexpr (ANC) {
                 if (fresh) read_shared();
-                const int next = task + KW;
-                if (next < ntask && (next < early || next >= pre1)) {
-                    locate(next);
-                    load_owners();   // in flight during the fold
-                }
+            }
+            // the next round's rows, or the table entries they are found by,
+            // are on their way during the fold
+            if (q0 + KW < ntask) {   // of the workgroup: no branch parts a wave from its loads
+                find(task + KW);
+                if constexpr (kAhead) fetch();
             }
 #pragma unroll
             for (int p = 0; p < kPer; ++p) {
@@ -1173,7 +1168,7 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typ
                     }
                 }
             }
-            if (q0 + KW < ntask || gb + kBatch < ngt) __syncthreads();
+            if (q0 + KW < ntask || gb + kBatch < ngt) lds_barrier();
             if (gb == 0 && q0 == 0) trace::stamp(trs, 5);
         }
     }
@@ -1291,15 +1286,14 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     const int lane = tid & (kWave - 1);
     const int w = wave_id();
 
+    const int t0 = j0 + w * kTile;
+    Rows rows;
+    if (t0 < j1) load_tile<D, BF16, false>(rows, K + (size_t)bh * S * kLpr, V + (size_t)bh * S * kLpr, t0, j1, lane);
     typename TL::Q qv;
     TL::load_q(qv, q, (size_t)b * KB, h, H, lane);
-    const uint4 *Kbh = K + (size_t)bh * S * kLpr;
-    const uint4 *Vbh = V + (size_t)bh * S * kLpr;
-
-    const int t0 = j0 + w * kTile;
     if (t0 < j1) {
         typename TL::St st;
-        TL::attend(qv, Kbh, Vbh, t0, j1, lane, &lds.t[w][0], scale_log2, st);
+        TL::attend(qv, rows, t0, j1, lane, &lds.t[w][0], scale_log2, st);
         TL::to_lds(st, lane, &lds.m[0][w], &lds.l[0][w], kWaves, lds.acc(w));
     }
     __syncthreads();
