@@ -104,14 +104,6 @@ unsigned long long call_epoch(hipStream_t s) {
     return capturing(s) ? 0ull : next_epoch();
 }
 
-// Decomposition of an attention call of n_bh rows over S keys (plus a
-// generated-token job); chosen once per call.
-fs::AttnPath attn_path_for(int n_bh, int S, int D, int esize, bool gen_job) {
-    const int C = fs::cross_attn_chunk_keys(D, esize);
-    const int NC = std::max(1, (S + C - 1) / C);
-    return fs::choose_attn_path(n_bh, NC + (gen_job ? 1 : 0));
-}
-
 // FS_VALIDATE's check of the device-resident lengths: a synchronous copy to
 // the host, refused while the stream is capturing (the copy and the
 // synchronisation would end the capture).
@@ -256,7 +248,7 @@ int fs_beam_cross_attn(const void *q, const void *K, const void *V, const int32_
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int esize = dtype == FS_BF16 ? 2 : 4;
-    const fs::AttnPath path = attn_path_for(B * H, S, D, esize, false);
+    const fs::AttnPath path = fs::choose_attn_path(B * H, S, D, esize, k, 0, false);
     if (validate_mode() && (st = validate_lengths(src_len, B, S, s, "src_len")) != FS_OK) return st;
     hipError_t e = fs::launch_cross_attn(q, K, V, src_len, out, B, k, H, S, D, dtype == FS_BF16,
                                          static_cast<float *>(workspace), call_epoch(s), s, path);
@@ -338,10 +330,11 @@ int decode_step(const void *q, const void *K, const void *V, const int32_t *src_
     const bool attn = B > 0 && k > 0 && H > 0;
     const bool ngram = rows > 0 && t >= n && vocab > 0;
     const int esize_i = dtype == FS_BF16 ? 2 : 4;
-    const fs::AttnPath path = attn ? attn_path_for(B * H, S, D, esize_i, false) : fs::AttnPath::kAuto;
+    const fs::AttnPath path = attn ? fs::choose_attn_path(B * H, S, D, esize_i, k, 0, false) : fs::AttnPath::kAuto;
     if (noalloc) {
-        // only the split-KV form keeps records; its need must fit the array
-        const size_t need = path == fs::AttnPath::kSplit
+        // only the split-KV form keeps records; what it needs for sizes it may
+        // be taken for must fit the array
+        const size_t need = path == fs::AttnPath::kSplit || (attn && fs::may_split(B * H, S, D, esize_i))
             ? fs::cross_attn_workspace_floats(B, k, H, S, D, esize_i, false) * sizeof(float) : 0;
         if (need > kScratchBytes)
             return fail(FS_ERR_UNSUPPORTED, "fs_beam_decode_step_noalloc: %d rows take the split-KV form, whose "
@@ -505,7 +498,7 @@ int prefix_attn(const void *q, const void *Kp, const void *Vp, const int32_t *pr
         return fail(FS_ERR_INVALID_ARG, "workspace overlaps an argument");
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const fs::AttnPath path = attn_path_for(B * H, N, D, dtype == FS_BF16 ? 2 : 4, t > 0);
+    const fs::AttnPath path = fs::choose_attn_path(B * H, N, D, (int)esize, k, t, indirect);
     if (validate_mode() && (st = validate_lengths(prefix_len, B, N, s, "prefix_len")) != FS_OK) return st;
     hipError_t e = fs::launch_prefix_attn(q, Kp, Vp, prefix_len, Kt, Vt, T, t, indirect && t > 0 ? anc : nullptr,
                                           ld_anc, out, B, k, H, N, D, dtype == FS_BF16,

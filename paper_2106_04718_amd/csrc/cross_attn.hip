@@ -55,7 +55,7 @@ constexpr int kBlock = kWave * kWaves;
 constexpr int kIt = 8;   // row loads of K (and of V) per lane per tile
 constexpr int kXcds = 8; // MI355X: workgroups go round-robin to 8 XCDs
 constexpr int kCus = 256;                // MI355X compute units
-constexpr int kWhole2MinRows = 128;      // fewer (b, h) rows than this are split across workgroups
+constexpr int kSplitMaxRows = 128;       // rows of many tiles are split across workgroups below this
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
@@ -1526,22 +1526,53 @@ AttnPath set_attn_path_override(AttnPath p) {
     return static_cast<AttnPath>(g_path_override.exchange(static_cast<int>(p), std::memory_order_relaxed));
 }
 
-AttnPath choose_attn_path(int n_bh, int jobs_max) {
+AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool table) {
     const AttnPath forced = static_cast<AttnPath>(g_path_override.load(std::memory_order_relaxed));
     if (forced != AttnPath::kAuto) return forced;
-    // Measured on MI355X (bf16, D = 64, k = 4 or 5; 192 to 5120 rows of up to
-    // 1024 keys): an 8-wave workgroup per row (two jobs in flight) is the
-    // fastest from 256 rows up (BART-shaped 512 rows: 18.6 us against 19.5
-    // for 4 waves; 5120 rows: 128 us against 134); with fewer rows than CUs
-    // a 16-wave workgroup per row uses the idle CUs' share of the row's
-    // jobs (192 rows of the split cache: 12.9 us against 13.9).  Rows of a
-    // single job take 4 waves, and only a few long rows are split across
-    // workgroups, whose merge costs a round trip through memory.
-    if (jobs_max <= 1) return AttnPath::kWhole1;
-    if (jobs_max <= 2) return AttnPath::kWhole2;
-    if (n_bh < kWhole2MinRows) return AttnPath::kSplit;
-    if (n_bh < kCus) return AttnPath::kWhole4;
-    return AttnPath::kWhole2;
+    // Wave tasks of a row at most: its prefix tiles, and its generated tiles
+    // once per beam (through a table, all but the last are mostly shared).
+    const int tile = cross_attn_chunk_keys(D, esize) / kWaves;
+    const long long nt = (S + tile - 1) / tile, ngt = (t + tile - 1) / tile;
+    const long long gen = ngt == 0 ? 0 : table ? ngt - 1 + k : ngt * k;
+    const long long tasks = nt + gen;
+    // The kernels that read through a table with D = 128 or in fp32 have more
+    // than 128 registers: three waves per SIMD.
+    const bool heavy = table && t > 0 && (D >= 128 || esize == 4);
+    // The lines below were measured on MI355X over 16 to 1024 rows, 128 to 2048
+    // keys, 0 to 500 generated tokens, D = 64 and 128, bf16 and f32 (graph
+    // replays of three rotated inputs).
+    if (n_bh > kCus) {
+        // More rows than CUs. Four waves where one round of four takes the row
+        // (1024 rows of 16 generated tokens: 8.5 us against 10.0 with eight),
+        // eight otherwise (768 rows of 512 keys: 12.6 against 13.5). Of three
+        // waves per SIMD, workgroups of eight leave a third unused (f32, 512
+        // rows, 500 tokens: 29.7 us with four against 40.4).
+        return tasks <= kWaves || heavy ? AttnPath::kWhole1 : AttnPath::kWhole2;
+    }
+    // A CU for every row: as many waves as the row has tasks, so that all of
+    // its loads are in flight at once.
+    if (tasks <= kWaves && table && t > 0) return AttnPath::kWhole1;
+    if (tasks <= 2 * kWaves) return AttnPath::kWhole2;
+    // Few rows of many tiles go to several workgroups each, whose records cost
+    // a round trip through memory (about 4 us): 64 rows of 2048 keys 12.2
+    // against 12.9 us, but 16 rows of 1024 keys 7.5 against 4.5, and, with the
+    // larger records of D = 128, 64 rows of 1024 keys 14.7 against 13.2.  The
+    // generated tokens all go to one of those workgroups: 64 more with f32,
+    // 2048 keys and 64 rows 18.4 against 30.4 us, but 300 more with 1024 keys
+    // in bf16 19.3 against 16.9.
+    if (n_bh < kSplitMaxRows) {
+        if (t > 0 ? nt >= 8 * kWaves && 2 * gen <= nt
+                  : nt > 8 * kWaves || (nt > 4 * kWaves && n_bh > 16 && D < 128))
+            return AttnPath::kSplit;
+    }
+    // Sixteen waves with D = 128 and a table spill: 256 rows of 256 + 64 rows
+    // 14.8 us against 10.9 with eight.
+    return heavy && esize == 2 ? AttnPath::kWhole2 : AttnPath::kWhole4;
+}
+
+bool may_split(int n_bh, int S, int D, int esize) {
+    return g_path_override.load(std::memory_order_relaxed) == static_cast<int>(AttnPath::kAuto) &&
+           n_bh < kSplitMaxRows && S > 2 * cross_attn_chunk_keys(D, esize);
 }
 
 int cross_attn_chunk_keys(int D, int esize) {

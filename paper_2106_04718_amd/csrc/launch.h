@@ -26,10 +26,15 @@ int cross_attn_chunk_keys(int D, int esize);
 //            time -- no records, needs many (b, h) rows to fill the chip.
 enum class AttnPath { kAuto = 0, kSplit, kWhole1, kWhole2, kWhole4 };
 
-// The path for n_bh = B*H rows of at most jobs_max jobs (chunks, plus the
-// generated tokens of the split cache): the size rule, unless a path was
-// forced with set_attn_path_override.
-AttnPath choose_attn_path(int n_bh, int jobs_max);
+// The path for n_bh = B*H rows of up to S keys, then (split cache) t generated
+// tokens of k beams, read directly or through an ancestry table: the size
+// rule, unless a path was forced with set_attn_path_override.
+AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool table);
+
+// Sizes the rule may give the split-KV form (fewer than 128 rows of more than
+// two chunks), unless a path was forced.  fs_beam_decode_step_noalloc answers
+// by this, so that what it refuses does not move with the rule.
+bool may_split(int n_bh, int S, int D, int esize);
 
 // Workgroup timelines of trace builds (trace.h): the buffer the attention
 // kernels and the selection kernel write (8 words per workgroup, `cap`
