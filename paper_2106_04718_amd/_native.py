@@ -4,8 +4,9 @@ Only argument marshalling lives here.  ``lib()`` is a ctypes handle on the
 library (every entry point, used for the size queries and the ABI tests);
 ``ext()`` is the CPython module built from csrc/pyext.c, which the launch
 calls go through because it converts arguments in a fraction of ctypes'
-time.  Both must have been built (``__graft_entry__.build()`` or
-``python -m paper_2106_04718_amd.build``); if either is missing every call
+time; ``fast()`` is the module built from csrc/torch_ext.cpp, which checks the
+tensors of a plain call in native code.  All must have been built (``__graft_entry__.build()`` or
+``python -m paper_2106_04718_amd.build``); if one is missing every call
 raises -- there is no fallback path.
 """
 import ctypes
@@ -62,6 +63,7 @@ SIGNATURES = [
 
 _lib = None
 _ext = None
+_fast = None
 
 
 class NativeError(RuntimeError):
@@ -101,6 +103,20 @@ def ext():
                                "(no CPU fallback exists for the decode-step kernels)") from e
         _ext = _fastseq_ext
     return _ext
+
+
+def fast():
+    """The native half of the tensor front end; raise if it was never built."""
+    global _fast
+    if _fast is None:
+        ext()
+        try:
+            from . import _fastseq_torch
+        except ImportError as e:
+            raise RuntimeError("the _fastseq_torch module is not built; run __graft_entry__.build() "
+                               "(no CPU fallback exists for the decode-step kernels)") from e
+        _fast = _fastseq_torch
+    return _fast
 
 
 def status_string(status: int) -> str:

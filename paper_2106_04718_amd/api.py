@@ -4,11 +4,13 @@ Each function checks tensor placement, dtype and layout, then passes raw
 device pointers and torch's current HIP stream to the C ABI.  PyTorch only
 provides memory and streams here; all arithmetic runs in the HIP kernels.
 
-A decode step is a few tens of microseconds of GPU time, so the per-call
-host work is kept small: workspace sizes are cached per shape, the stream
-handle is read without building a Stream object, the device is switched
-only when the tensors are not on the current one, and the call itself goes
-through the CPython marshalling module rather than ctypes.
+A decode step is a few tens of microseconds of GPU time, a small one 5, so the
+per-call host work is kept small: a call that passes its outputs and workspace
+is checked and made in one native step (csrc/torch_ext.cpp; 7 to 9 us a call
+from Python alone became 4.3, most of it the launch).  Whatever that step does not take as it is --
+outputs to allocate, a device to switch to, an argument to reject -- goes the
+general way below, where workspace sizes are cached per shape and the call
+goes through the CPython marshalling module rather than ctypes.
 """
 from __future__ import annotations
 
@@ -21,6 +23,15 @@ from . import _native as _N
 _native_lib = _N.lib
 _DTYPES = {torch.float32: _N.FS_F32, torch.bfloat16: _N.FS_BF16}
 _WS_BYTES: dict = {}
+
+_fast = None
+
+
+def _load_fast():
+    global _fast
+    _fast = _N.fast()
+    return _fast
+
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _cur_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
@@ -85,6 +96,12 @@ def beam_cross_attn(q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, src_len: 
     :func:`new_workspace`, zero-filled once, then reused) avoids an
     allocation and a fill per call.
     """
+    if out is not None and workspace is not None:
+        st = (_fast or _load_fast()).beam_cross_attn(q, K, V, src_len, out, workspace)
+        if st is not None:
+            if st:
+                _N.check(st)
+            return out
     for name, t in (("q", q), ("K", K), ("V", V), ("src_len", src_len)):
         _need_cuda(name, t)
     if q.dim() != 4 or K.dim() != 4 or K.shape != V.shape:
@@ -127,6 +144,13 @@ def beam_decode_step(q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, src_len:
     :func:`ngram_block` on the step's B*k hypotheses (tokens [B*k, ld],
     logits [B*k, vocab], modified in place).  Bit for bit the two calls.
     Returns ``out``."""
+    if out is not None and workspace is not None and (t is None or t >= 0):
+        st = (_fast or _load_fast()).beam_decode_step(q, K, V, src_len, tokens, n, logits, -1 if t is None else t,
+                                                      out, workspace)
+        if st is not None:
+            if st:
+                _N.check(st)
+            return out
     for name, x in (("q", q), ("K", K), ("V", V), ("src_len", src_len)):
         _need_cuda(name, x)
     _need_cuda("logits", logits)
@@ -254,6 +278,12 @@ def beam_prefix_attn(q: torch.Tensor, Kp: torch.Tensor, Vp: torch.Tensor, prefix
     generated row tau of hypothesis b*k + i is read from the block of
     hypothesis b*k + anc[b*k + i, tau] instead of its own.
     """
+    if out is not None and workspace is not None:
+        st = (_fast or _load_fast()).beam_prefix_attn(q, Kp, Vp, prefix_len, Kt, Vt, t, out, workspace, anc)
+        if st is not None:
+            if st:
+                _N.check(st)
+            return out
     for name, x in (("q", q), ("Kp", Kp), ("Vp", Vp), ("prefix_len", prefix_len), ("Kt", Kt), ("Vt", Vt)):
         _need_cuda(name, x)
     if q.dim() != 4 or Kp.dim() != 4 or Kp.shape != Vp.shape or Kt.dim() != 4 or Kt.shape != Vt.shape:
@@ -309,6 +339,11 @@ def ancestry_step(anc: torch.Tensor, parent: torch.Tensor, k: int, t: int) -> to
     of b*k + parent[b*k + j]; column t becomes j (its new token, written to
     its own row).  Returns anc.
     """
+    st = (_fast or _load_fast()).ancestry_step(anc, parent, k, t)
+    if st is not None:
+        if st:
+            _N.check(st)
+        return anc
     _need_cuda("anc", anc)
     _need_cuda("parent", parent)
     if anc.dtype != torch.int32 or anc.dim() != 2 or k < 1 or anc.shape[0] % k:
@@ -332,6 +367,12 @@ def ngram_block(tokens: torch.Tensor, n: int, logits: torch.Tensor, t: int | Non
     history, default all); logits [rows, V] float32, contiguous.  Returns
     ``logits`` with banned entries set to -inf.
     """
+    if t is None or t >= 0:
+        st = (_fast or _load_fast()).ngram_block(tokens, n, logits, -1 if t is None else t)
+        if st is not None:
+            if st:
+                _N.check(st)
+            return logits
     if not isinstance(tokens, torch.Tensor) or tokens.device.type != "cuda":
         raise ValueError("tokens must be a GPU tensor")
     _need_cuda("logits", logits)
@@ -379,6 +420,13 @@ def beam_select(logits: torch.Tensor, beam_scores: torch.Tensor, k: int, c: int,
     beam_score + log-softmax candidates, best first, ties to the smaller
     flat index beam*V + token.  ``out`` may pass the three output tensors.
     """
+    if out is not None and workspace is not None and len(out) == 3 and (t is None or t >= 0):
+        st = (_fast or _load_fast()).beam_select(logits, beam_scores, k, c, tokens, n, -1 if t is None else t,
+                                                 out[0], out[1], out[2], workspace)
+        if st is not None:
+            if st:
+                _N.check(st)
+            return out
     _need_cuda("logits", logits)
     _need_cuda("beam_scores", beam_scores)
     if logits.dim() != 2 or logits.dtype != torch.float32:
@@ -435,6 +483,12 @@ def cache_reorder(K: torch.Tensor, V: torch.Tensor | None, parent: torch.Tensor,
     b*k + parent[b*k + j]; other rows, and beams whose parent is themselves or
     outside [0, k), keep their bytes.
     """
+    if V is not None and (t is None or t >= 0):
+        st = (_fast or _load_fast()).cache_reorder(K, V, parent, k, -1 if t is None else t)
+        if st is not None:
+            if st:
+                _N.check(st)
+            return
     _need_cuda("K", K)
     _need_cuda("parent", parent)
     if K.dim() != 4 or K.dtype not in _DTYPES or not K.is_contiguous():

@@ -5,7 +5,8 @@ instructions are disabled for device code (``-packed-fp32-ops``); the host
 pass warns that it does not know that feature, which is harmless.
 
 The CPython marshalling module (csrc/pyext.c, plain C) is then compiled with
-gcc and linked against the library.
+gcc and linked against the library, and so is the tensor front end's native
+half (csrc/torch_ext.cpp, C++ against the installed torch's headers).
 
 ``build(trace=True)`` (``--trace``) compiles every source with FS_TRACE=1: the
 attention and selection kernels then write per-workgroup timelines to a
@@ -33,6 +34,7 @@ BUILD = PKG / "_build"
 LIB = PKG / "libfastseq_hip.so"
 EXT = PKG / ("_fastseq_ext" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["capi.cpp", "cross_attn.hip", "ngram_block.hip", "beam_select.hip", "cache_reorder.hip", "postproc.cpp"]  # pyext.c is built by build_ext
+TORCH_EXT = PKG / ("_fastseq_torch" + sysconfig.get_config_var("EXT_SUFFIX"))
 ARCH = "gfx950"
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -87,7 +89,8 @@ def _compile(src: str, verbose: bool, sanitize: bool = False, trace: bool = Fals
 
 def build(verbose: bool = False, sanitize: bool = False, trace: bool = False) -> pathlib.Path:
     BUILD.mkdir(exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        front = ex.submit(compile_torch_ext, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose, sanitize, trace), SOURCES))
     tmp = str(LIB) + ".tmp"
     cmd = [hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", "-Wl,-soname,libfastseq_hip.so",
@@ -97,6 +100,7 @@ def build(verbose: bool = False, sanitize: bool = False, trace: bool = False) ->
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
     build_ext(verbose, sanitize)
+    link_torch_ext(front.result(), verbose)
     return LIB
 
 
@@ -113,6 +117,33 @@ def build_ext(verbose: bool = False, sanitize: bool = False) -> pathlib.Path:
     subprocess.run(cmd, check=True)
     os.replace(tmp, EXT)
     return EXT
+
+
+def compile_torch_ext(verbose: bool = False) -> pathlib.Path:
+    """Object file of the tensor front end's native half (never sanitized: torch is not)."""
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    obj = BUILD / "torch_ext.o"
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-Wall", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-isystem{p}" for p in include_paths()), f"-I{sysconfig.get_paths()['include']}",
+           f"-I{ROOT / 'include'}", "-c", str(CSRC / "torch_ext.cpp"), "-o", str(obj)]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return obj
+
+
+def link_torch_ext(obj: pathlib.Path, verbose: bool = False) -> pathlib.Path:
+    from torch.utils.cpp_extension import library_paths
+    tmp = str(TORCH_EXT) + ".tmp"
+    cmd = ["g++", "-shared", str(obj), f"-L{PKG}", "-lfastseq_hip", *(f"-L{p}" for p in library_paths()),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, TORCH_EXT)
+    return TORCH_EXT
 
 
 if __name__ == "__main__":

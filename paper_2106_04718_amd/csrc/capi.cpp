@@ -103,6 +103,10 @@ bool capturing(hipStream_t s) {
 unsigned long long call_epoch(hipStream_t s) {
     return capturing(s) ? 0ull : next_epoch();
 }
+// An attention call: only the split-KV form exchanges records.
+unsigned long long attn_epoch(hipStream_t s, fs::AttnPath path) {
+    return path == fs::AttnPath::kSplit ? call_epoch(s) : 0ull;
+}
 
 // FS_VALIDATE's check of the device-resident lengths: a synchronous copy to
 // the host, refused while the stream is capturing (the copy and the
@@ -251,7 +255,7 @@ int fs_beam_cross_attn(const void *q, const void *K, const void *V, const int32_
     const fs::AttnPath path = fs::choose_attn_path(B * H, S, D, esize, k, 0, false);
     if (validate_mode() && (st = validate_lengths(src_len, B, S, s, "src_len")) != FS_OK) return st;
     hipError_t e = fs::launch_cross_attn(q, K, V, src_len, out, B, k, H, S, D, dtype == FS_BF16,
-                                         static_cast<float *>(workspace), call_epoch(s), s, path);
+                                         static_cast<float *>(workspace), attn_epoch(s, path), s, path);
     if (e != hipSuccess) return hip_fail(e, "fs_beam_cross_attn launch");
     return FS_OK;
 }
@@ -374,7 +378,7 @@ int decode_step(const void *q, const void *K, const void *V, const int32_t *src_
     if (noalloc && path == fs::AttnPath::kSplit && (st = scratch_on(s, &workspace)) != FS_OK) return st;
     const fs::NgramRows ng{tokens, ld_tokens, rows, t, n, logits, vocab};
     hipError_t e = fs::launch_cross_attn(q, K, V, src_len, out, B, k, H, S, D, dtype == FS_BF16,
-                                         static_cast<float *>(workspace), call_epoch(s), s, path,
+                                         static_cast<float *>(workspace), attn_epoch(s, path), s, path,
                                          ngram ? &ng : nullptr);
     if (e != hipSuccess) return hip_fail(e, noalloc ? "fs_beam_decode_step_noalloc launch" : "fs_beam_decode_step launch");
     return FS_OK;
@@ -502,7 +506,7 @@ int prefix_attn(const void *q, const void *Kp, const void *Vp, const int32_t *pr
     if (validate_mode() && (st = validate_lengths(prefix_len, B, N, s, "prefix_len")) != FS_OK) return st;
     hipError_t e = fs::launch_prefix_attn(q, Kp, Vp, prefix_len, Kt, Vt, T, t, indirect && t > 0 ? anc : nullptr,
                                           ld_anc, out, B, k, H, N, D, dtype == FS_BF16,
-                                          static_cast<float *>(workspace), call_epoch(s), s, path);
+                                          static_cast<float *>(workspace), attn_epoch(s, path), s, path);
     if (e != hipSuccess) return hip_fail(e, indirect ? "fs_beam_prefix_attn_indirect launch" : "fs_beam_prefix_attn launch");
     return FS_OK;
 }
