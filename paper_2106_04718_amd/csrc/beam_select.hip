@@ -59,6 +59,31 @@ constexpr int kMaxSpins = 1 << 14;       // bounded re-reads of a record word (a
 constexpr int kNMax = 8;                 // n-gram sizes whose first window is loaded ahead
 constexpr int kWaves = kThreads / kWave;
 constexpr int kBlocks = kWave / kWaves;   // threshold blocks per wave: 64 in a workgroup
+constexpr int kSpan = kThreads * 4;       // window positions one load instruction of the workgroup covers
+constexpr int kGroupsMax = kPer / 4;      // 16-byte loads per thread at most
+
+// n / d for 0 <= n < 2^31 by a multiplication (d fixed on the host): mul =
+// floor(2^(31 + l) / d) + 1 with l = ceil(log2 d).
+struct Div {
+    unsigned mul;
+    int shift;
+    __device__ __forceinline__ unsigned operator()(unsigned n) const {
+        return (unsigned)(((unsigned long long)n * mul) >> shift);
+    }
+};
+inline Div make_div(int d) {
+    int l = 0;
+    while (l < 31 && (1ll << l) < d) ++l;
+    return Div{(unsigned)((1ull << (31 + l)) / (unsigned)d + 1), 31 + l};
+}
+
+// Maximum of three; fmaxf on loaded values first quiets them, one instruction
+// each (the logits are finite or -inf).
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 
 #if FS_TRACE
 __device__ trace::Target g_trace{nullptr, 0};
@@ -195,12 +220,11 @@ __device__ __forceinline__ uint32_t buf_load(__amdgpu_buffer_rsrc_t r, int voff,
 __host__ __device__ constexpr int rec_words(int c) { return 2 + 2 * c; }
 
 // The c best of n keys in LDS, by rank: thread e counts the keys above key
-// e, and a key of rank < c goes to out[rank] (keys other than 0 are
-// distinct, so the ranks are).  keys is 16-byte aligned and, for odd n,
-// keys[n] is 0 (a 0 key is above none); out[0..c) must hold 0 beforehand.
-// The keys are read two at a time, eight reads in flight.
-__device__ __forceinline__ void rank_top_keys(const unsigned long long *keys, int n, int c,
-                                              unsigned long long *out) {
+// e, and put(rank, key) takes a key of rank < c (the keys are distinct and
+// not 0, so the ranks are).  keys is 16-byte aligned and, for odd n, keys[n]
+// is 0 (above none).  The keys are read two at a time, eight reads in flight.
+template <class Put>
+__device__ __forceinline__ void rank_keys(const unsigned long long *keys, int n, int c, const Put &put) {
     const ulonglong2 *k2 = reinterpret_cast<const ulonglong2 *>(keys);
     const int n2 = (n + 1) / 2;
     for (int e = threadIdx.x; e < n; e += kThreads) {
@@ -218,7 +242,7 @@ __device__ __forceinline__ void rank_top_keys(const unsigned long long *keys, in
             const ulonglong2 q = k2[j];
             rank += (q.x > ke) + (q.y > ke);
         }
-        if (rank < c && ke != 0ull) out[rank] = ke;
+        if (rank < c) put(rank, ke);
     }
 }
 
@@ -248,7 +272,7 @@ __device__ __forceinline__ float block_max(float x) {
 // other, so the kernel holds them in one union.
 struct SliceLds {
     alignas(16) unsigned long long comp[kCap + 2 + kWave];  // candidate keys, then one spare slot per lane
-    alignas(16) unsigned long long bkey[kWave];     // the 64 block maxima as keys
+    uint32_t bmax[kWave];                           // the 64 block maxima, ordered
     unsigned long long best[16];
     unsigned long long xwin[kWaves];                // exact path: each wave's best key of a round
     uint32_t ban_bits[kSliceMax / 32];
@@ -259,10 +283,9 @@ struct SliceLds {
 struct MergeLds {
     alignas(16) unsigned long long keys[kMergeCap + 2];
     alignas(16) unsigned long long surv[kMergeCap + 2];
-    unsigned long long best[16];
     unsigned long long hc;
     uint32_t w32[kMergeWords];
-    float bsc[16];
+    float bsc[16], lse[16];
     int stale, nsurv;
 };
 union SelectLds {
@@ -280,16 +303,19 @@ union SelectLds {
 // so no read leaves the pages of the logits.
 __device__ __forceinline__ constexpr int offs(int j) { return (j / 4) * kThreads * 4 + j % 4; }
 
-__device__ void select_slice(SliceLds &L, const float *__restrict__ logits, const int32_t *__restrict__ tokens,
-                             int ld, int t, int n, unsigned long long *__restrict__ part, int r, int s, int V, int c,
-                             int NS, int SL, unsigned long long tag)
+// kGroups: the loads a slice of this call can need (1 .. kGroupsMax); every
+// step runs over all of them, without a branch per load.
+template <int kGroups>
+__device__ __forceinline__ void select_slice(SliceLds &L, const float *__restrict__ logits,
+                                             const int32_t *__restrict__ tokens, int ld, int t, int n,
+                                             unsigned long long *__restrict__ part, int r, int s, int V, int c,
+                                             int NS, int SL, unsigned long long tag)
 {
-    constexpr int kGroups = kPer / 4;          // 16-byte loads per thread
-    constexpr int kSpan = kThreads * 4;        // window positions per load
+    constexpr int kVals = 4 * kGroups;
     constexpr float kLog2e = 1.4426950408889634f;
     uint32_t *ban_bits = L.ban_bits;
     int *nban = L.nban;
-    unsigned long long *comp = L.comp, *best = L.best, *bkey = L.bkey, *xwin = L.xwin;
+    unsigned long long *comp = L.comp, *best = L.best, *xwin = L.xwin;
     float *wm = L.wm, *ws = L.ws;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -301,7 +327,6 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
     const float *x = logits + (size_t)r * V + v0;
     const int a = (int)((reinterpret_cast<uintptr_t>(x) >> 2) & 3);
     const int wl = len > 0 ? a + len : 0;                 // window length (an empty slice reads nothing)
-    const int ng = (wl + kSpan - 1) / kSpan;              // loads holding any slice position
     const int nfull = wl / kSpan;                         // loads [a ? 1 : 0, nfull) hold only slice positions
     const int lbase = tid * 4;
 
@@ -319,7 +344,7 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
     for (int q = 0; q < kNMax; ++q) hw[q] = (int32_t)buf_load(tres, (tid + q) * 4, 0, 0);
 #pragma unroll
     for (int q = 0; q < kNMax - 1; ++q) sf[q] = (int32_t)buf_load(tres, (t - n + 1 + q) * 4, 0, 0);
-    float val[kPer];
+    float val[kVals];
     {
         const auto res = buf_rsrc(x - a, wl * 4);
 #pragma unroll
@@ -373,34 +398,33 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
     float gm[kGroups];   // maximum of each load's four values
 #pragma unroll
     for (int g = 0; g < kGroups; ++g) {
-        gm[g] = -INFINITY;
-        if (g < ng) {
-            if (g >= nfull || (g == 0 && a != 0)) {
+        if (g >= nfull || (g == 0 && a != 0)) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    val[4 * g + e] = (unsigned)(lbase + offs(4 * g + e) - a) < (unsigned)len ? val[4 * g + e]
-                                                                                          : -INFINITY;
-            }
-            gm[g] = fmaxf(fmaxf(val[4 * g], val[4 * g + 1]), fmaxf(val[4 * g + 2], val[4 * g + 3]));
-            m = fmaxf(m, gm[g]);
+            for (int e = 0; e < 4; ++e)
+                val[4 * g + e] = (unsigned)(lbase + offs(4 * g + e) - a) < (unsigned)len ? val[4 * g + e] : -INFINITY;
         }
+        gm[g] = max3(max3(val[4 * g], val[4 * g + 1], val[4 * g + 2]), val[4 * g + 3], val[4 * g + 3]);
+        m = max3(m, gm[g], gm[g]);
     }
-    // the wave's (max, sum of exp) over every logit, banned or not
-    const float mw = wave_max_f(m);
     if (trs) {
-        asm volatile("" ::"v"(mw));   // the stamp after the data
+        asm volatile("" ::"v"(m));   // the stamp after the data
         trace::stamp(trs, 1);
     }
-    float sum = 0.f;
-    if (mw != -INFINITY) {
-        const float sh = mw * kLog2e;
+    // The lane's sum of exp over every logit, banned or not, against the
+    // lane's own maximum: no reduction stands before it.  Four chains.
+    float sl = 0.f;
+    {
+        const float sh = m == -INFINITY ? 0.f : m * kLog2e;
+        float s4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int g = 0; g < kGroups; ++g)
-            if (g < ng)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum += __builtin_amdgcn_exp2f(fmaf(val[4 * g + e], kLog2e, -sh));
+            for (int e = 0; e < 4; ++e) s4[e] += __builtin_amdgcn_exp2f(fmaf(val[4 * g + e], kLog2e, -sh));
+        sl = (s4[0] + s4[1]) + (s4[2] + s4[3]);
     }
-    const float sw = wave_sum_f(sum);
+    // taken here: left to the compiler it moves behind the bans, and the values
+    // from before and after them are both live
+    asm volatile("" : "+v"(sl));
 
     // Banned positions cannot be candidates: with any ban in the slice, every
     // wave turns its banned values into -inf (after the sums, which take
@@ -414,24 +438,26 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
         cm = -INFINITY;
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
-            if (g < ng) {
-                const uint32_t bits = ban_bits[(lbase + g * kSpan) >> 5] >> ((lbase + g * kSpan) & 31);
+            const uint32_t bits = g * kSpan < wl ? ban_bits[(lbase + g * kSpan) >> 5] >> ((lbase + g * kSpan) & 31) : 0u;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) val[4 * g + e] = ((bits >> e) & 1u) ? -INFINITY : val[4 * g + e];
-                gm[g] = fmaxf(fmaxf(val[4 * g], val[4 * g + 1]), fmaxf(val[4 * g + 2], val[4 * g + 3]));
-                cm = fmaxf(cm, gm[g]);
-            }
+            for (int e = 0; e < 4; ++e) val[4 * g + e] = ((bits >> e) & 1u) ? -INFINITY : val[4 * g + e];
+            gm[g] = max3(max3(val[4 * g], val[4 * g + 1], val[4 * g + 2]), val[4 * g + 3], val[4 * g + 3]);
+            cm = max3(cm, gm[g], gm[g]);
         }
     }
-    // Threshold tau: the c-th largest of the slice's 64 block maxima (blocks
-    // of kWaves adjacent lanes of one wave, so kBlocks per wave).  The c
-    // largest blocks each hold a distinct unbanned position at or above tau,
-    // so the slice's c best candidates all lie at or above it.  Each lane
-    // ranks one block maximum (as a key with its block index, so the 64 keys
-    // are distinct) against all 64; every wave finds the same tau.
+    // Threshold tau: at most the c-th largest of the slice's 64 block maxima
+    // (blocks of kWaves adjacent lanes of one wave, so kBlocks per wave).  The
+    // c largest blocks each hold a distinct unbanned position at or above it,
+    // so the slice's c best candidates all lie at or above it.  Every wave
+    // finds it by itself, the highest kTauBits of it one by one: a bit stays
+    // set while c block maxima reach the prefix (a ballot and a count per
+    // bit, where ranking the 64 maxima through LDS took 1 us).  The bits left
+    // out lower it by less than 2^-11 of its value.
     const float bm = block_max(cm);
-    const int bidx = wv * kBlocks + lane / kWaves;
-    if ((lane & (kWaves - 1)) == 0) bkey[bidx] = ((unsigned long long)ordered(bm) << 32) | (uint32_t)~bidx;
+    if ((lane & (kWaves - 1)) == 0) L.bmax[wv * kBlocks + lane / kWaves] = ordered(bm);
+    // the wave's (max, sum of exp)
+    const float mw = wave_max_f(m);
+    const float sw = wave_sum_f(m == -INFINITY ? 0.f : sl * __builtin_amdgcn_exp2f((m - mw) * kLog2e));
     if (lane == 0) {
         wm[wv] = mw;
         ws[wv] = sw;
@@ -439,21 +465,15 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
     lds_barrier();
     float tau;
     {
-        const unsigned long long mine = bkey[lane];
-        const ulonglong2 *b2 = reinterpret_cast<const ulonglong2 *>(bkey);
-        // four reads in flight at a time
-        int rank = 0;
+        constexpr int kTauBits = 20;
+        const uint32_t mine = L.bmax[lane];
+        uint32_t T = 0u;
 #pragma unroll
-        for (int q0 = 0; q0 < kWave / 2; q0 += 4) {
-            ulonglong2 o[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) o[u] = b2[q0 + u];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) rank += (o[u].x > mine) + (o[u].y > mine);
+        for (int bit = 31; bit > 31 - kTauBits; --bit) {
+            const uint32_t up = T | (1u << bit);
+            T = __popcll(__builtin_amdgcn_ballot_w64(mine >= up)) >= c ? up : T;
         }
-        const unsigned long long at = __builtin_amdgcn_ballot_w64(rank == c - 1);
-        const int src = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(at));   // one lane: the keys are distinct
-        tau = unordered((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), src));
+        tau = T > ordered(-INFINITY) ? unordered(T) : -INFINITY;
     }
     if (trs) {
         asm volatile("" ::"v"(tau));
@@ -469,14 +489,14 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
     if (tau == -INFINITY) {
 #pragma unroll
         for (int g = 0; g < kGroups; ++g)
-            if (g < ng && (g >= nfull || (g == 0 && a != 0)))
+            if (g >= nfull || (g == 0 && a != 0))
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     val[4 * g + e] = (unsigned)(lbase + offs(4 * g + e) - a) < (unsigned)len ? val[4 * g + e] : NAN;
     }
     uint32_t lhot = 0u;   // this lane's loads holding a value at or above tau
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) lhot |= (g < ng && gm[g] >= tau) ? 1u << g : 0u;
+    for (int g = 0; g < kGroups; ++g) lhot |= gm[g] >= tau ? 1u << g : 0u;
     const uint32_t hot = __builtin_amdgcn_readfirstlane(wave_or(lhot));
     int nh = 0;
 #pragma unroll
@@ -532,7 +552,7 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
             }
             if (tid < 16) best[tid] = 0ull;
             lds_barrier();
-            rank_top_keys(comp, total, c, best);
+            rank_keys(comp, total, c, [&](int at, unsigned long long key) { best[at] = key; });
         } else {
             // Exact path (more than kCap values at the threshold, e.g. equal
             // logits): c rounds, each taking the best key below the last one.
@@ -559,7 +579,7 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
                 // positions outside the slice (high half 0) never rise above it
                 uint32_t bh = 0u, bl = ~0u;
 #pragma unroll
-                for (int j = 0; j < kPer; ++j) {
+                for (int j = 0; j < kVals; ++j) {
                     const uint32_t hi = __float_as_uint(val[j]);
                     const uint32_t lo = lo0 - (uint32_t)offs(j);
                     const bool below = hi < last_hi || (hi == last_hi && lo < last_lo);
@@ -611,13 +631,14 @@ __device__ void select_slice(SliceLds &L, const float *__restrict__ logits, cons
 __device__ void select_merge(MergeLds &L, const float *__restrict__ beam_scores,
                              const unsigned long long *__restrict__ part, float *__restrict__ out_scores,
                              int32_t *__restrict__ out_beam, int32_t *__restrict__ out_token, int b, int k, int V,
-                             int c, int NS, unsigned long long tag)
+                             int c, int NS, Div by_NS, Div by_c, Div by_V, unsigned long long tag)
 {
     uint32_t *w32 = L.w32;
     float *bsc = L.bsc;
-    unsigned long long *keys = L.keys, *surv = L.surv, *best = L.best;
+    unsigned long long *keys = L.keys, *surv = L.surv;
     int &stale = L.stale;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int W = rec_words(c);
     const int nw = k * NS * W;
     const unsigned long long *recs = part + (size_t)b * k * NS * W;
@@ -630,17 +651,16 @@ __device__ void select_merge(MergeLds &L, const float *__restrict__ beam_scores,
         L.nsurv = 0;
         L.hc = 0ull;
     }
-    if (tid < 16) best[tid] = 0ull;
     if (tid < k) bsc[tid] = beam_scores[(size_t)b * k + tid];
     // the survivors' array holds 0 past its last entry (a 0 key ranks below
     // every other), so no entry needs clearing after the packing
     for (int e = tid; e < kMergeCap + 2; e += kThreads) surv[e] = 0ull;
     constexpr int kPerThread = kMergeWords / kThreads;
-    unsigned long long wv[kPerThread];
+    unsigned long long word[kPerThread];
 #pragma unroll
     for (int q = 0; q < kPerThread; ++q) {
         const int e = tid + q * kThreads;
-        wv[q] = e < nw ? __hip_atomic_load(recs + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
+        word[q] = e < nw ? __hip_atomic_load(recs + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
     }
     // re-read every word still without the tag together, so the wait ends
     // one round trip after the last record lands
@@ -648,55 +668,78 @@ __device__ void select_merge(MergeLds &L, const float *__restrict__ beam_scores,
     for (int spin = 0; spin < kMaxSpins; ++spin) {
         bool pending = false;
 #pragma unroll
-        for (int q = 0; q < kPerThread; ++q) pending |= (wv[q] & kHi) != tag;
+        for (int q = 0; q < kPerThread; ++q) pending |= (word[q] & kHi) != tag;
         if (!pending) break;
         __builtin_amdgcn_s_sleep(2);
 #pragma unroll
         for (int q = 0; q < kPerThread; ++q)
-            if ((wv[q] & kHi) != tag)
-                wv[q] = __hip_atomic_load(recs + tid + q * kThreads, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((word[q] & kHi) != tag)
+                word[q] = __hip_atomic_load(recs + tid + q * kThreads, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     bool old = false;
 #pragma unroll
     for (int q = 0; q < kPerThread; ++q) {
         const int e = tid + q * kThreads;
-        old |= (wv[q] & kHi) != tag;
-        if (e < nw) w32[e] = (uint32_t)wv[q];
+        old |= (word[q] & kHi) != tag;
+        if (e < nw) w32[e] = (uint32_t)word[q];
     }
     __syncthreads();
     trace::stamp(trs, 1);
     if (old) stale = 1;
-    // Every slice candidate, scored; each thread takes its row's lse from the
-    // row's slice records (the maximum, then the rescaled sums in slice
-    // order).  Keys are stored position-major, key (j, record q) at
-    // j * nrec + q, so the records' heads (j = 0) are the first nrec keys.
     const int ncand = k * NS * c;
     const int nrec = k * NS;
     constexpr float kL2e = 1.4426950408889634f;
-    for (int e = tid; e < ncand; e += kThreads) {
-        const int i = e / (NS * c), rem = e - i * NS * c, s = rem / c, j = rem - s * c;
+    // Each row's lse from its slices' (max, sum): one wave per row, a lane per
+    // slice (each candidate's thread walking its row's slices took 3 us with
+    // 28 of them).
+    for (int i = wv; i < k; i += kWaves) {
         const uint32_t *rw = w32 + i * NS * W;
         float M = -INFINITY;
-        for (int u = 0; u < NS; ++u) M = fmaxf(M, __uint_as_float(rw[u * W]));
+        for (int u = lane; u < NS; u += kWave) M = fmaxf(M, __uint_as_float(rw[u * W]));
+        M = wave_max_f(M);
         float S = 0.f;
-        for (int u = 0; u < NS; ++u) {
+        for (int u = lane; u < NS; u += kWave) {
             const float ms = __uint_as_float(rw[u * W]);
-            const float ss = __uint_as_float(rw[u * W + 1]);
-            S += ms == -INFINITY ? 0.f : ss * __builtin_amdgcn_exp2f((ms - M) * kL2e);
+            S += ms == -INFINITY ? 0.f : __uint_as_float(rw[u * W + 1]) * __builtin_amdgcn_exp2f((ms - M) * kL2e);
         }
-        const float lr = M == -INFINITY ? -INFINITY : M + logf(S);
-        const float x = __uint_as_float(rw[s * W + 2 + j]);
-        const uint32_t v = rw[s * W + 2 + c + j];
+        S = wave_sum_f(S);
+        if (lane == 0) L.lse[i] = M == -INFINITY ? -INFINITY : M + logf(S);
+    }
+    __syncthreads();
+    // Every slice candidate, scored.  Keys are stored position-major, key (j,
+    // record q) at j * nrec + q, so the records' heads (j = 0) are the first
+    // nrec keys.
+    for (int e = tid; e < ncand; e += kThreads) {
+        const int q = (int)by_c((unsigned)e), j = e - q * c, i = (int)by_NS((unsigned)q);
+        const float lr = L.lse[i];
+        const float x = __uint_as_float(w32[q * W + 2 + j]);
+        const uint32_t v = w32[q * W + 2 + c + j];
         const float sc = (lr == -INFINITY || x == -INFINITY) ? -INFINITY : bsc[i] + (x - lr);
         // an empty slot (v = ~0) ranks below every candidate
-        keys[j * nrec + i * NS + s] = v == 0xffffffffu ? 0ull : make_key(sc, (uint32_t)i * (uint32_t)V + v);
+        keys[j * nrec + q] = v == 0xffffffffu ? 0ull : make_key(sc, (uint32_t)i * (uint32_t)V + v);
     }
     __syncthreads();
     // Prune: the heads (first candidates) of the k * NS records are distinct
     // candidates, so no candidate below the c-th largest head is among the c
     // best.  The heads are ranked among themselves, the candidates at or
     // above that head are packed, and only they are ranked.
-    if (nrec >= c) {
+    unsigned long long hc = 0ull;
+    if (nrec >= c && nrec <= kWave) {
+        // every wave by itself, a lane per record
+        const ulonglong2 *h2 = reinterpret_cast<const ulonglong2 *>(keys);
+        const unsigned long long hq = lane < nrec ? keys[lane] : 0ull;
+        int rank = 0;
+        for (int q2 = 0; 2 * q2 < nrec; ++q2) {
+            const ulonglong2 o = h2[q2];
+            rank += (o.x > hq) + (2 * q2 + 1 < nrec && o.y > hq);
+        }
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(hq != 0ull && rank == c - 1);   // one lane or none
+        if (at != 0ull) {
+            const int src = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(at));
+            hc = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(hq >> 32), src) << 32) |
+                 (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)hq, src);
+        }
+    } else if (nrec >= c) {
         const ulonglong2 *h2 = reinterpret_cast<const ulonglong2 *>(keys);
         for (int q = tid; q < nrec; q += kThreads) {
             const unsigned long long hq = keys[q];
@@ -710,8 +753,8 @@ __device__ void select_merge(MergeLds &L, const float *__restrict__ beam_scores,
             if (rank == c - 1) L.hc = hq;   // heads other than 0 are distinct
         }
         __syncthreads();
+        hc = L.hc;
     }
-    const unsigned long long hc = L.hc;
     for (int e0 = 0; e0 < ncand; e0 += kThreads) {
         const int e = e0 + tid;
         const unsigned long long ke = e < ncand ? keys[e] : 0ull;
@@ -725,38 +768,48 @@ __device__ void select_merge(MergeLds &L, const float *__restrict__ beam_scores,
                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = ke;
     }
     __syncthreads();
+    // Each survivor's rank; those below c write their place.
     const int ns = L.nsurv;
-    rank_top_keys(surv, ns, c, best);
-    __syncthreads();
-    if (tid < c) {
-        const unsigned long long kk = best[tid];
-        const uint32_t f = ~(uint32_t)kk;
-        const bool bad = stale || kk == 0ull;
-        out_scores[(size_t)b * c + tid] = bad ? NAN : unordered((uint32_t)(kk >> 32));
-        out_beam[(size_t)b * c + tid] = bad ? -1 : (int32_t)(f / (uint32_t)V);
-        out_token[(size_t)b * c + tid] = bad ? -1 : (int32_t)(f % (uint32_t)V);
-    }
+    const bool bad = stale != 0;
+    auto put = [&](int at, unsigned long long key) {
+        const uint32_t f = ~(uint32_t)key;
+        const bool none = bad || key == 0ull;
+        const uint32_t i = k == 1 ? 0u : f < 0x80000000u ? by_V(f) : f / (uint32_t)V;
+        out_scores[(size_t)b * c + at] = none ? NAN : unordered((uint32_t)(key >> 32));
+        out_beam[(size_t)b * c + at] = none ? -1 : (int32_t)i;
+        out_token[(size_t)b * c + at] = none ? -1 : (int32_t)(f - i * (uint32_t)V);
+    };
+    rank_keys(surv, ns, c, put);
+    if (tid >= ns && tid < c) put(tid, 0ull);   // fewer candidates than c
     trace::stamp(trs, 4);
     trace::put(trs, 5, trace::where());
     trace::put(trs, 6, (unsigned long long)ns);
     trace::put(trs, 7, 1);
 }
 
-__global__ __launch_bounds__(kThreads) void beam_select_kernel(
-    const float *__restrict__ logits, const float *__restrict__ beam_scores, const int32_t *__restrict__ tokens,
-    int ld, int t, int n, float *__restrict__ out_scores, int32_t *__restrict__ out_beam,
-    int32_t *__restrict__ out_token, unsigned long long *__restrict__ part, int rows, int k, int V, int c,
-    int NS, int SL, unsigned long long epoch, unsigned long long *__restrict__ ctr)
+// Eight waves per SIMD: four slice workgroups on a CU, so that their loads,
+// barriers and ranks overlap (three, at 70 registers, ran 1280 rows of 50264
+// logits in 65 us; four in 51 us).
+template <int kGroups>
+__global__ __launch_bounds__(kThreads, 8) void beam_select_kernel(
+    const float *__restrict__ logits, const int32_t *__restrict__ tokens, unsigned long long *__restrict__ part,
+    int ld, int t, int n, int V, int NS, int SL, unsigned ns_mul, int ns_shift,
+    int rows, int k, int c, unsigned k_mul, int k_shift, unsigned c_mul, int c_shift, unsigned v_mul, int v_shift,
+    const float *__restrict__ beam_scores, float *__restrict__ out_scores, int32_t *__restrict__ out_beam,
+    int32_t *__restrict__ out_token, unsigned long long epoch, unsigned long long *__restrict__ ctr)
 {
     __shared__ SelectLds lds;
     const int g = blockIdx.x;
-    const int b = g < rows * NS ? g / NS / k : g - rows * NS;
+    const Div by_NS{ns_mul, ns_shift}, by_k{k_mul, k_shift};
+    const int r = (int)by_NS((unsigned)g);
+    const int b = g < rows * NS ? (int)by_k((unsigned)r) : g - rows * NS;
     unsigned long long c0 = 0;
     const unsigned long long tag = call_tag(epoch, ctr + b, c0);
     if (g < rows * NS) {
-        select_slice(lds.slice, logits, tokens, ld, t, n, part, g / NS, g % NS, V, c, NS, SL, tag);
+        select_slice<kGroups>(lds.slice, logits, tokens, ld, t, n, part, r, g - r * NS, V, c, NS, SL, tag);
     } else {
-        select_merge(lds.merge, beam_scores, part, out_scores, out_beam, out_token, b, k, V, c, NS, tag);
+        select_merge(lds.merge, beam_scores, part, out_scores, out_beam, out_token, b, k, V, c, NS, by_NS,
+                     Div{c_mul, c_shift}, Div{v_mul, v_shift}, tag);
         // a captured call: the merger has every record (or its wait ran
         // out), so every slice of the source has read the counter; the next
         // call takes the next value (skipping one after a wait that ran out,
@@ -788,17 +841,27 @@ int set_select_slices_override(int slices) {
 }
 
 int beam_select_slices(int rows, int V, int k, int c) {
-    // About kTargetWorkgroups slice workgroups, slices of at least 1024
-    // logits, and no more than one merger ranks; a slice's window (slice plus
-    // up to 3 leading positions) fits the kSliceMax positions of a workgroup.
+    // One slice workgroup per CU, slices of at least 1024 logits, at most
+    // kMergeRecords records for a merger, and no more than one ranks; a
+    // slice's window (slice plus up to 3 leading positions) fits the kSliceMax
+    // positions of a workgroup.  Measured with k = 4, c = 8 (us): 4 sources of
+    // 32128 logits 9.0 with 8 slices per row, 9.4 with 16, 10.7 with 28 (the
+    // records one merger reads); 8 sources of 50264 10.0 with 8, 11.0 with 16;
+    // 16 sources 10.8 with 4, 11.5 with 8; 320 sources 54 with the 4 that
+    // 16381 positions allow, 66 with 6 (each slice pays its barriers again).
     // set_select_slices_override sets the count within the same limits.
-    constexpr int kTargetWorkgroups = 512;
+    constexpr int kTargetWorkgroups = 256;
+    constexpr int kMergeRecords = 32;
     const int by_size = (V + kSliceMax - 4) / (kSliceMax - 3);
     const int by_cand = kMergeCap / (k * c > 0 ? k * c : 1);
     const int by_words = kMergeWords / (k * rec_words(c) > 0 ? k * rec_words(c) : 1);
     const int forced = g_slices_override.load(std::memory_order_relaxed);
     int ns = forced > 0 ? forced : (kTargetWorkgroups + rows - 1) / (rows > 0 ? rows : 1);
-    if (forced <= 0) ns = ns < (V + 1023) / 1024 ? ns : (V + 1023) / 1024;
+    if (forced <= 0) {
+        const int by_records = kMergeRecords / k > 0 ? kMergeRecords / k : 1;
+        ns = ns < (V + 1023) / 1024 ? ns : (V + 1023) / 1024;
+        ns = ns < by_records ? ns : by_records;
+    }
     ns = ns < by_cand ? ns : by_cand;
     ns = ns < by_words ? ns : by_words;
     ns = ns < V ? ns : V;
@@ -823,9 +886,22 @@ hipError_t launch_beam_select(const float *logits, const float *beam_scores, con
     const int SL = (V + NS - 1) / NS;
     const long long nblk = (long long)rows * NS + B;
     unsigned long long *ctr = workspace + (size_t)rows * NS * rec_words(c);
-    hipLaunchKernelGGL(beam_select_kernel, dim3((unsigned)nblk), dim3(kThreads), 0, stream, logits, beam_scores,
-                       tokens, ld, t, n, out_scores, out_beam, out_token, workspace, rows, k, V, c, NS, SL, epoch,
-                       ctr);
+    const Div ns = make_div(NS), dk = make_div(k), dc = make_div(c), dv = make_div(V);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(kThreads), 0, stream, logits, tokens, workspace, ld, t,
+                           n, V, NS, SL, ns.mul, ns.shift, rows, k, c, dk.mul, dk.shift, dc.mul, dc.shift, dv.mul,
+                           dv.shift, beam_scores, out_scores, out_beam, out_token, epoch, ctr);
+    };
+    switch ((SL + 3 + kSpan - 1) / kSpan) {   // loads of a slice's window, up to 3 positions before it
+    case 1: launch(beam_select_kernel<1>); break;
+    case 2: launch(beam_select_kernel<2>); break;
+    case 3: launch(beam_select_kernel<3>); break;
+    case 4: launch(beam_select_kernel<4>); break;
+    case 5: launch(beam_select_kernel<5>); break;
+    case 6: launch(beam_select_kernel<6>); break;
+    case 7: launch(beam_select_kernel<7>); break;
+    default: launch(beam_select_kernel<kGroupsMax>); break;
+    }
     return hipGetLastError();
 }
 

@@ -1,0 +1,57 @@
+"""fs_beam_select over the sizes of its slice windows: every number of loads a
+thread takes, at the edges where it changes, from rows that start at each
+offset from 16 bytes; few and many records per merger; heavy masks and equal
+logits in each.  Against the oracle, with the tolerance of the other tests of
+the call (a few roundings of an fp32 log-normaliser).
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2106_04718_amd import api
+
+from _gpu import device, say
+from test_gpu_select import check, random_case
+
+pytestmark = pytest.mark.gpu
+
+
+# a window of one slice is V + 3 positions at most, 2048 per load
+@pytest.mark.parametrize("loads", range(1, 9))
+def test_each_window_size_at_its_edges(loads):
+    for V in (2048 * loads - 5, 2048 * loads - 4, 2048 * loads - 3, 2048 * (loads - 1) + 9):
+        with api.select_slices(1):
+            d = random_case(2, 3, V, 20, seed=loads * 10 + V % 7)
+            check(d, 3, 6, 3, 20, f"one slice, V={V}")
+            d = random_case(2, 3, V, 12, seed=V, neg_inf=0.999)     # a few finite logits per row
+            check(d, 3, 5, 2, 12, f"one slice, V={V}, mostly -inf")
+            d["logits"][:] = np.where(np.isinf(d["logits"]), -np.inf, np.float32(0.5))   # and those equal
+            check(d, 3, 5, 2, 12, f"one slice, V={V}, equal")
+
+
+@pytest.mark.parametrize("k,slices,c", [(1, 64, 8), (1, 65, 8), (2, 33, 4), (4, 16, 16), (5, 13, 8), (16, 4, 16),
+                                        (1, 1, 16), (3, 22, 15)])
+def test_records_of_a_merger(k, slices, c):
+    # up to 64 records are pruned by every wave on its own, more through LDS
+    with api.select_slices(slices):
+        d = random_case(3, k, 5003 + slices, 30, seed=k * 100 + slices)
+        check(d, k, c, 2, 30, f"k={k} slices={slices} c={c}")
+
+
+def test_threshold_between_close_values():
+    # values that differ only below the threshold's leading 20 bits, of both
+    # signs: more candidates are collected, the picks stay the same
+    dev = device()
+    rng = np.random.default_rng(3)
+    for sign in (1.0, -1.0):
+        x = np.float32(sign) * (np.float32(4.0) + rng.permutation(6000).astype(np.float32) * np.float32(4.8e-7))
+        lg = torch.from_numpy(x[None]).to(dev)
+        say(f"[select threshold] sign={sign}")
+        s, i, v = api.beam_select(lg, torch.zeros(1, device=dev), 1, 16)
+        torch.cuda.synchronize()
+        # equal values after the subtraction of the normaliser resolve to the smaller index
+        sc = s.cpu().numpy()[0]
+        assert np.all(np.diff(sc) <= 0)
+        got = x[v.cpu().numpy()[0]]
+        want = np.sort(x)[::-1][:16]
+        assert np.all(np.abs(got - want) <= np.spacing(np.float32(12.7)))   # one rounding of x - lse, lse < 12.71
