@@ -900,14 +900,17 @@ struct GenRows {
 
 // LDS of a workgroup of KW waves that walks a row: each wave's tile area
 // (which then holds its acc for the fold), its (max, sum) per beam, and for
-// generated tiles the beam its task belongs to (-1: every beam) and, per tile
-// of a batch, whether the beams share it.
-template <int D, bool BF16, int KB, int KW>
+// generated tiles the beam its task belongs to (-1: every beam) and, with an
+// ancestry table (ANC), per tile of a batch whether the beams share it and the
+// owners of its rows if so.
+template <int D, bool BF16, int KB, int KW, bool ANC>
 struct RowLds {
     __attribute__((aligned(16))) float m[KB][KW], l[KB][KW];
     __attribute__((aligned(16))) char t[KW][WaveLds<D, BF16, KB>::kBytes];
     int task[KW];
-    unsigned char shared[kWave];
+    // (tiles of more rows, D = 16 and 32 in bf16, would not fit beside 16 waves)
+    static constexpr bool kOwners = ANC && Geo<D, BF16>::kTile <= kWave;
+    unsigned char shared[kWave], owner[kOwners ? kWave : 1][Geo<D, BF16>::kTile];
     __device__ __forceinline__ float *acc(int w) { return reinterpret_cast<float *>(&t[w][0]); }
 };
 
@@ -947,7 +950,7 @@ struct OutState {
 // waves reads slowly (192 rows of up to 1024 prefix keys, 64 generated, k = 4:
 // 12.0 us, against 12.2 us with every generated tile after the prefix).
 template <int D, bool BF16, int KB, int KW, bool GEN, bool ANC>
-__device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typename Tile<D, BF16, KB>::Q &qv,
+__device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, const typename Tile<D, BF16, KB>::Q &qv,
                                          const uint4 *__restrict__ q, const uint4 *__restrict__ Kbh,
                                          const uint4 *__restrict__ Vbh, int L, int b, int h, int H, const GenRows &gr,
                                          float scale_log2, OutState<(KB * D + KW * kWave - 1) / (KW * kWave)> &R,
@@ -990,18 +993,20 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typ
         const int pre1 = early + npre;   // end of the prefix tasks
         unsigned long long sh = 0;      // tiles of the batch with one owner per row for every beam
         int ntask = npre + ng * KB;
-        // Does tile jt of the batch have one owner per row?  (one wave per tile)
+        // Does tile jt of the batch have one owner per row?  (one wave per
+        // tile, which leaves the owners in LDS)
         auto mark_shared = [&]() {
             for (int jt = w; jt < ng; jt += KW) {
                 bool same = KB == 1 || gb + jt < ngt - 1;
                 for (int p = lane; same && p < kTile; p += kWave) {
-                    const int j = (gb + jt) * kTile + p;   // < t: not the last tile
+                    const int j = min((gb + jt) * kTile + p, gr.t - 1);   // past t with one beam only
                     const int32_t *col = gr.anc + hyp0 * gr.ld + j;
                     int a[KB];
 #pragma unroll
                     for (int i = 0; i < KB; ++i) a[i] = col[(size_t)i * gr.ld];
 #pragma unroll
                     for (int i = 1; i < KB; ++i) same &= owner(a[i], i) == owner(a[0], 0);
+                    if (RowLds<D, BF16, KB, KW, ANC>::kOwners) lds.owner[jt][p] = (unsigned char)owner(a[0], 0);
                 }
                 const bool all = __builtin_amdgcn_ballot_w64(!same) == 0ull;
                 if (lane == 0) lds.shared[jt] = all;
@@ -1051,9 +1056,14 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typ
             t0 = (gb + g_tile) * kTile;
             j1 = gr.t;
             if constexpr (ANC) {
-                const int32_t *row = gr.anc + (hyp0 + max(g_beam, 0)) * gr.ld;
+                if (RowLds<D, BF16, KB, KW, ANC>::kOwners && g_beam < 0) {
 #pragma unroll
-                for (int u = 0; u < kIt; ++u) own[u] = row[min(t0 + u * kRpi + lane / kLpr, gr.t - 1)];
+                    for (int u = 0; u < kIt; ++u) own[u] = lds.owner[g_tile][u * kRpi + lane / kLpr];
+                } else {
+                    const int32_t *row = gr.anc + (hyp0 + max(g_beam, 0)) * gr.ld;
+#pragma unroll
+                    for (int u = 0; u < kIt; ++u) own[u] = row[min(t0 + u * kRpi + lane / kLpr, gr.t - 1)];
+                }
             }
             if constexpr (!kOwnIsTile) {
                 if (g_beam >= 0) TO::load_q(qo, q, hyp0 + g_beam, h, H, lane);
@@ -1181,7 +1191,7 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW> &lds, const typ
 // Generated-token segment of (b, h) = bh (SPLIT only): its state goes to
 // record slot NT of (b, h).
 template <int D, bool BF16, int KB, bool ANC>
-__device__ __forceinline__ void attend_generated(RowLds<D, BF16, KB, kWaves> &lds, const uint4 *__restrict__ q,
+__device__ __forceinline__ void attend_generated(RowLds<D, BF16, KB, kWaves, ANC> &lds, const uint4 *__restrict__ q,
                                                  unsigned long long *__restrict__ part, int bh, int n_bh, int H,
                                                  Div by_H, int NT, const GenRows &gr, float scale_log2,
                                                  unsigned long long epoch,
@@ -1236,7 +1246,7 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
         return;
     }
 
-    __shared__ RowLds<D, BF16, KB, kWaves> lds;
+    __shared__ RowLds<D, BF16, KB, kWaves, ANC> lds;
 
     // Workgroup g runs on XCD g % 8 (round-robin dispatch).  All chunks of
     // one (b, h), its generated-token workgroup and its merger get ids with
@@ -1343,7 +1353,7 @@ __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
     constexpr int kThreads = kBlock * P;
     constexpr int kPer = (KB * D + kThreads - 1) / kThreads;  // outputs per thread
 
-    __shared__ RowLds<D, BF16, KB, kW> lds;
+    __shared__ RowLds<D, BF16, KB, kW, ANC> lds;
 
     const Div by_H{h_mul, h_shift};
     // A fused decode step's n-gram rows take the first workgroups.
