@@ -1367,7 +1367,8 @@ __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
     trace::stamp(trs, 0);
     const int b = by_H(bh);
     const int h = bh - b * H;
-    const int L = min(max(src_len[b], 0), S);
+    int L = 0;
+    if (!SPLIT || S > 0) L = min(max(src_len[b], 0), S);   // without a prefix, no trip to memory for its length
     const int tid = threadIdx.x;
     const size_t obase = ((size_t)b * KB * H + h) * D;  // out[b, 0, h, 0]
     typename TL::Q qv;
