@@ -71,9 +71,14 @@ def sanitizer_runtime() -> str:
                           capture_output=True, text=True).stdout.strip()
 
 
-def _compile(src: str, verbose: bool, sanitize: bool = False, trace: bool = False) -> pathlib.Path:
-    obj = BUILD / (src + ".o")
-    cmd = [hipcc(), *COMMON, *(SANITIZE_HOST if sanitize else []), *(["-DFS_TRACE=1"] if trace else []),
+# (source, defines) of every object: the attention kernels' instances, by far
+# the longest to compile, are built in four parts side by side
+OBJECTS = [(s, ()) for s in SOURCES] + [("cross_attn.hip", (f"-DFS_ATTN_PART={part}",)) for part in (1, 2, 3)]
+
+
+def _compile(src: str, defines: tuple, verbose: bool, sanitize: bool = False, trace: bool = False) -> pathlib.Path:
+    obj = BUILD / (src + "".join(d.replace("-D", ".").replace("=", "") for d in defines) + ".o")
+    cmd = [hipcc(), *COMMON, *defines, *(SANITIZE_HOST if sanitize else []), *(["-DFS_TRACE=1"] if trace else []),
            "-x", "hip", "-c", str(CSRC / src), "-o", str(obj)]
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -89,9 +94,9 @@ def _compile(src: str, verbose: bool, sanitize: bool = False, trace: bool = Fals
 
 def build(verbose: bool = False, sanitize: bool = False, trace: bool = False) -> pathlib.Path:
     BUILD.mkdir(exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=len(OBJECTS) + 1) as ex:
         front = ex.submit(compile_torch_ext, verbose)
-        objs = list(ex.map(lambda s: _compile(s, verbose, sanitize, trace), SOURCES))
+        objs = list(ex.map(lambda o: _compile(*o, verbose, sanitize, trace), OBJECTS))
     tmp = str(LIB) + ".tmp"
     cmd = [hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", "-Wl,-soname,libfastseq_hip.so",
            *(SANITIZE_LINK if sanitize else []), *map(str, objs), "-o", tmp]

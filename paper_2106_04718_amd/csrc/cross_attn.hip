@@ -1398,6 +1398,8 @@ __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
     trace::put(trs, 4, (unsigned long long)njobs);
 }
 
+}  // namespace
+
 // Launch arguments shared by both entry points.  For the encoder-decoder
 // form Kt/Vt are null and T = t = 0.
 struct AttnArgs {
@@ -1415,6 +1417,8 @@ struct AttnArgs {
     NgramJob ng;          // n-gram rows of a fused decode step (ng.rows == 0: none)
     AttnPath path;        // decomposition chosen for the call
 };
+
+namespace {
 
 template <int D, bool BF16, int KB, bool SPLIT, bool ANC = false>
 hipError_t launch_split(const AttnArgs &a, int NC)
@@ -1518,11 +1522,22 @@ hipError_t launch_d(const AttnArgs &a)
 
 }  // namespace
 
-namespace {
-std::atomic<int> g_path_override{0};
-}  // namespace
-
-hipError_t set_attn_trace(unsigned long long *buf, unsigned int cap) {
+// This file is compiled once per part -- 0: bf16 encoder-decoder and the host
+// functions, 1: f32 encoder-decoder, 2: bf16 split cache, 3: f32 split cache --
+// so that the kernels' instances build side by side.
+#ifndef FS_ATTN_PART
+#define FS_ATTN_PART 0
+#endif
+template <int PART>
+hipError_t launch_part(const AttnArgs &a);
+template <int PART>
+hipError_t trace_part(unsigned long long *buf, unsigned int cap);
+template <>
+hipError_t launch_part<FS_ATTN_PART>(const AttnArgs &a) {
+    return launch_d<FS_ATTN_PART % 2 == 0, (FS_ATTN_PART >= 2)>(a);
+}
+template <>
+hipError_t trace_part<FS_ATTN_PART>(unsigned long long *buf, unsigned int cap) {
 #if FS_TRACE
     const trace::Target t{buf, cap};
     return hipMemcpyToSymbol(HIP_SYMBOL(g_trace), &t, sizeof(t));
@@ -1531,6 +1546,32 @@ hipError_t set_attn_trace(unsigned long long *buf, unsigned int cap) {
     (void)cap;
     return hipErrorNotSupported;
 #endif
+}
+
+#if FS_ATTN_PART == 0
+template <>
+hipError_t launch_part<1>(const AttnArgs &a);
+template <>
+hipError_t launch_part<2>(const AttnArgs &a);
+template <>
+hipError_t launch_part<3>(const AttnArgs &a);
+template <>
+hipError_t trace_part<1>(unsigned long long *buf, unsigned int cap);
+template <>
+hipError_t trace_part<2>(unsigned long long *buf, unsigned int cap);
+template <>
+hipError_t trace_part<3>(unsigned long long *buf, unsigned int cap);
+
+namespace {
+std::atomic<int> g_path_override{0};
+}  // namespace
+
+hipError_t set_attn_trace(unsigned long long *buf, unsigned int cap) {
+    hipError_t e = trace_part<0>(buf, cap);
+    if (e == hipSuccess) e = trace_part<1>(buf, cap);
+    if (e == hipSuccess) e = trace_part<2>(buf, cap);
+    if (e == hipSuccess) e = trace_part<3>(buf, cap);
+    return e;
 }
 
 AttnPath set_attn_path_override(AttnPath p) {
@@ -1610,7 +1651,7 @@ hipError_t launch_cross_attn(const void *q, const void *K, const void *V, const 
                NgramJob{nullptr, nullptr, 0, 0, 0, 0, 0, 0}, path};
     if (ngram)
         a.ng = NgramJob{ngram->tokens, ngram->logits, ngram->ld, ngram->t, ngram->n - 1, ngram->V, ngram->rows, 0};
-    return bf16 ? launch_d<true, false>(a) : launch_d<false, false>(a);
+    return bf16 ? launch_part<0>(a) : launch_part<1>(a);
 }
 
 hipError_t launch_prefix_attn(const void *q, const void *Kp, const void *Vp, const int32_t *prefix_len,
@@ -1620,7 +1661,8 @@ hipError_t launch_prefix_attn(const void *q, const void *Kp, const void *Vp, con
 {
     const AttnArgs a{q, Kp, Vp, prefix_len, out, B, k, H, N, D, Kt, Vt, T, t, anc, ld_anc, workspace, epoch, stream,
                      NgramJob{nullptr, nullptr, 0, 0, 0, 0, 0, 0}, path};
-    return bf16 ? launch_d<true, true>(a) : launch_d<false, true>(a);
+    return bf16 ? launch_part<2>(a) : launch_part<3>(a);
 }
+#endif  // FS_ATTN_PART == 0
 
 }  // namespace fs
