@@ -281,7 +281,20 @@ PyObject *ancestry_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
                                                  (int)(anc.size(0) / k), (int)k, (int)t, s));
 }
 
-#define FS_FAST(f) (PyCFunction)(void (*)(void)) f, METH_FASTCALL
+// A torch accessor throws for a tensor whose data must not be touched (one made
+// by a tracer, for instance); no exception may cross into the interpreter, so
+// such a call is declined too and the general path raises torch's own error.
+using Fast = PyObject *(PyObject *, PyObject *const *, Py_ssize_t);
+template <Fast F>
+PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) noexcept {
+    try {
+        return F(self, a, n);
+    } catch (...) {
+        return declined();
+    }
+}
+
+#define FS_FAST(f) (PyCFunction)(void (*)(void)) guarded<f>, METH_FASTCALL
 PyMethodDef methods[] = {
     {"beam_cross_attn", FS_FAST(cross_attn), "(q, K, V, src_len, out, workspace) -> status, or None: not the plain case"},
     {"beam_decode_step", FS_FAST(decode_step), "(q, K, V, src_len, tokens, n, logits, t or -1, out, workspace)"},

@@ -43,6 +43,13 @@ def raw(t):
     return str(t.dtype), tuple(t.shape), c.view(torch.uint8).numpy().tobytes() if c.numel() else b""
 
 
+def sealed(x):
+    """A tensor whose data pointer torch refuses to give (it throws)."""
+    x = x.clone()
+    torch._C._set_throw_on_mutable_data_ptr(x)
+    return x
+
+
 def wide(x):
     """The same values with a leading dimension past the columns."""
     return torch.cat([x, x], dim=1)[:, :x.shape[1]]
@@ -74,6 +81,7 @@ CHANGES = {
     "anc ld": lambda x: dict(anc=wide(x["anc"])), "anc rows": lambda x: dict(anc=x["anc"][:5].contiguous()),
     "q strided": lambda x: dict(q=x["q"].transpose(1, 2).contiguous().transpose(1, 2)),
     "q f32": lambda x: dict(q=x["q"].float()), "q parameter": lambda x: dict(q=torch.nn.Parameter(x["q"])),
+    "sealed": lambda x: dict(q=sealed(x["q"]), tok=sealed(x["tok"]), par=sealed(x["par"])),
     "K 3d": lambda x: dict(K=x["K"][0]), "K cut": lambda x: dict(K=x["K"][:, :, :60].contiguous()),
     "len int64": lambda x: dict(ln=x["ln"].long()), "len 3": lambda x: dict(ln=x["ln"].repeat(2)[:3]),
     "out f32": lambda x: dict(out=x["out"].float()), "out none": dict(out=None), "so two": lambda x: dict(so=x["so"][:2]),
