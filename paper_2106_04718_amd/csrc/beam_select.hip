@@ -27,8 +27,8 @@
 //   * one merger workgroup per source, after all slice workgroups in the
 //     grid, combines the slices' (max, sum) into each row's lse, scores the
 //     k * slices * c candidates and keeps the c best.
-// Each logit costs about five vector instructions (a max, a fused scale,
-// an exp, an add and a compare), which keeps the slice pass under the time
+// Each logit costs about six vector instructions (a max, a subtraction, a
+// scale, an exp, an add and a compare), which keeps the slice pass under the time
 // its bytes take to arrive.
 // Candidates are compared as 64-bit keys (order-preserving bits of the value,
 // then the complement of the flat index), so equal values resolve to the
@@ -411,15 +411,19 @@ __device__ __forceinline__ void select_slice(SliceLds &L, const float *__restric
         trace::stamp(trs, 1);
     }
     // The lane's sum of exp over every logit, banned or not, against the
-    // lane's own maximum: no reduction stands before it.  Four chains.
+    // lane's own maximum: no reduction stands before it.  Four chains.  The
+    // maximum is subtracted before the scaling, so that every exponent is at
+    // most 0 and the largest is 0, however large the logits: a lane of mask
+    // values alone (-1e10, the type's lowest) would otherwise sum the powers of
+    // what its rounded product is off by, to infinity.
     float sl = 0.f;
     {
-        const float sh = m == -INFINITY ? 0.f : m * kLog2e;
+        const float sh = m == -INFINITY ? 0.f : m;
         float s4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int g = 0; g < kGroups; ++g)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s4[e] += __builtin_amdgcn_exp2f(fmaf(val[4 * g + e], kLog2e, -sh));
+            for (int e = 0; e < 4; ++e) s4[e] += __builtin_amdgcn_exp2f((val[4 * g + e] - sh) * kLog2e);
         sl = (s4[0] + s4[1]) + (s4[2] + s4[3]);
     }
     // taken here: left to the compiler it moves behind the bans, and the values

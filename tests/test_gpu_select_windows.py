@@ -29,6 +29,45 @@ def test_each_window_size_at_its_edges(loads):
             check(d, 3, 5, 2, 12, f"one slice, V={V}, equal")
 
 
+MASKS = (-1e4, -1e9, -1e10, -1e30, float(np.finfo(np.float32).min))
+
+
+@pytest.mark.parametrize("loads", range(1, 9))
+def test_finite_mask_values(loads):
+    # whole lanes, and whole waves, of one mask value beside ordinary logits:
+    # a lane's own maximum is then the mask value, whose product with log2 e
+    # rounds by more than the exponent's range (or overflows)
+    V = 2048 * loads - 3
+    rng = np.random.default_rng(loads)
+    for mask in MASKS:
+        for what, share in (("90 %", 0.9), ("99.9 %", 0.999), ("a run", 0.0)):
+            d = random_case(2, 3, V, 12, seed=loads)
+            if share:
+                d["logits"][rng.random(d["logits"].shape) < share] = mask
+            else:
+                d["logits"][:, V // 8:] = mask
+            d["logits"][:, 1:9] = np.linspace(0.0, 1.0, 8, dtype=np.float32)   # picks that are no mask value
+            with api.select_slices(1):
+                check(d, 3, 6, 2, 12, f"one slice, V={V}, {what} {mask}")
+
+
+def test_rows_of_one_finite_value():
+    # every logit of a row the same: the normaliser is that value plus log V,
+    # held in fp32, so a score is off by its rounding at that value's size
+    dev = device()
+    V = 5003
+    for x in MASKS + (0.0, 1e30):
+        lg = torch.full((6, V), x, device=dev)
+        bs = torch.tensor([-1.0, -2.0, -3.0, -1.5, -1.5, -1.5], device=dev)
+        say(f"[select parity] rows of {x}")
+        s, i, v = (o.cpu().numpy() for o in api.beam_select(lg, bs, 3, 6))
+        assert np.isfinite(s).all()
+        want = bs.cpu().numpy().reshape(2, 3)[np.arange(2)[:, None], i] - np.log(V)
+        assert np.all(np.abs(s - want) <= 1e-5 * (1 + np.abs(want)) + np.spacing(np.float32(abs(x)))), x
+        for b in range(2):
+            assert len({(int(p), int(w)) for p, w in zip(i[b], v[b])}) == 6 and v[b].min() >= 0 and v[b].max() < V
+
+
 @pytest.mark.parametrize("k,slices,c", [(1, 64, 8), (1, 65, 8), (2, 33, 4), (4, 16, 16), (5, 13, 8), (16, 4, 16),
                                         (1, 1, 16), (3, 22, 15)])
 def test_records_of_a_merger(k, slices, c):
