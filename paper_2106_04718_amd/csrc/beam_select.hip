@@ -461,7 +461,8 @@ __device__ __forceinline__ void select_slice(SliceLds &L, const float *__restric
     if ((lane & (kWaves - 1)) == 0) L.bmax[wv * kBlocks + lane / kWaves] = ordered(bm);
     // the wave's (max, sum of exp)
     const float mw = wave_max_f(m);
-    const float sw = wave_sum_f(m == -INFINITY ? 0.f : sl * __builtin_amdgcn_exp2f((m - mw) * kLog2e));
+    // (a lane of -inf alone has the factor 0 by itself; a NaN stays one)
+    const float sw = wave_sum_f(mw == -INFINITY ? 0.f : sl * __builtin_amdgcn_exp2f((m - mw) * kLog2e));
     if (lane == 0) {
         wm[wv] = mw;
         ws[wv] = sw;

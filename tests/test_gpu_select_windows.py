@@ -68,6 +68,22 @@ def test_rows_of_one_finite_value():
             assert len({(int(p), int(w)) for p, w in zip(i[b], v[b])}) == 6 and v[b].min() >= 0 and v[b].max() < V
 
 
+def test_nan_beside_masked_logits_reaches_the_scores():
+    # a NaN logit must not pass for a masked one: the row has no normaliser, so
+    # none of its scores is a number, whatever the other logits of its lane are
+    dev = device()
+    V = 4099
+    for rest in (-np.inf, 0.5):
+        for at in (1000, 1003, 4098):
+            lg = torch.full((2, V), rest, device=dev)
+            lg[:, 960:1100:20] = 1.0       # ordinary logits in the lanes about it
+            lg[:, 4060:4096:20] = 1.0
+            lg[0, at] = float("nan")
+            say(f"[select parity] NaN at {at}, rest {rest}")
+            s = api.beam_select(lg, torch.zeros(2, device=dev), 1, 4)[0].cpu().numpy()
+            assert not np.isfinite(s[0]).any() and np.isfinite(s[1]).all(), (at, rest, s)
+
+
 @pytest.mark.parametrize("k,slices,c", [(1, 64, 8), (1, 65, 8), (2, 33, 4), (4, 16, 16), (5, 13, 8), (16, 4, 16),
                                         (1, 1, 16), (3, 22, 15)])
 def test_records_of_a_merger(k, slices, c):
