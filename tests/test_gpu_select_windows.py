@@ -10,6 +10,7 @@ import torch
 
 from paper_2106_04718_amd import api
 
+import test_gpu_select
 from _gpu import device, say
 from test_gpu_select import check, random_case
 
@@ -82,6 +83,52 @@ def test_nan_beside_masked_logits_reaches_the_scores():
             say(f"[select parity] NaN at {at}, rest {rest}")
             s = api.beam_select(lg, torch.zeros(2, device=dev), 1, 4)[0].cpu().numpy()
             assert not np.isfinite(s[0]).any() and np.isfinite(s[1]).all(), (at, rest, s)
+
+
+def test_common_offset_costs_nothing():
+    # scores that spread little about a large common value reach the same few
+    # candidates as the same scores about 0: not the c rounds over every value
+    # that equal logits need (2.5 times as long at these sizes)
+    dev = device()
+    B, k, V, c = 32, 4, 50264, 8
+    g = torch.Generator(device=dev).manual_seed(5)
+    x = torch.randn(B * k, V, device=dev, generator=g)
+    bs = torch.zeros(B * k, device=dev)
+    out = (torch.empty(B, c, device=dev), torch.empty(B, c, dtype=torch.int32, device=dev),
+           torch.empty(B, c, dtype=torch.int32, device=dev))
+    ws = api.new_workspace(api.beam_select_workspace_bytes(B, k, V, c), dev)
+
+    def time_of(lg):
+        best = float("inf")
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(20):
+                api.beam_select(lg, bs, k, c, out=out, workspace=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    ref = time_of(x)
+    for off in (4e3, 1e4, -1e4, 1e5):
+        say(f"[select time] offset {off}")
+        assert time_of(x + off) < 1.5 * ref, off
+
+
+@pytest.mark.parametrize("offset", [0.0, 4e3, 1e4, -1e4])
+@pytest.mark.parametrize("step", [0.0, 2.0 ** -10, 2.0 ** -8, 1.0])
+def test_offset_logits_of_few_values(offset, step, monkeypatch):
+    # ties, and values that the threshold's first bits do not tell apart, around
+    # the counts at which the threshold is finished and at which the exact path runs
+    # (the fp32 normaliser is off by one rounding at the logits' size)
+    size = np.spacing(np.float32(abs(offset) + 300 * step))
+    monkeypatch.setattr(test_gpu_select, "tol", lambda v: 1e-5 * (1.0 + np.abs(v)) + size)
+    for V, seed in ((4099, 1), (16381, 2)):
+        d = random_case(2, 2, V, 12, seed=seed)
+        d["logits"] = (np.float32(offset) + np.float32(step) * np.floor(d["logits"] * 64)).astype(np.float32)
+        with api.select_slices(1):
+            check(d, 2, 8, 2, 12, f"V={V}, offset {offset}, steps of {step}")
 
 
 @pytest.mark.parametrize("k,slices,c", [(1, 64, 8), (1, 65, 8), (2, 33, 4), (4, 16, 16), (5, 13, 8), (16, 4, 16),
