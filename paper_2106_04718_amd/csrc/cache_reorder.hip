@@ -119,9 +119,11 @@ hipError_t launch_chunks(unsigned char *K, unsigned char *V, const int32_t *pare
     const unsigned nblk = (unsigned)((nq + kThreads - 1) / kThreads);
     constexpr int kMaxY = 65535, kMaxZ = 65535;   // grid limits: more sources or heads take more launches
     const int tensors = V ? 2 : 1, step = kMaxZ / tensors;
-    for (int b0 = 0; b0 < B; b0 += step) {
-        for (int h0 = 0; h0 < H; h0 += kMaxY) {
-            const int nb = B - b0 < step ? B - b0 : step, nh = H - h0 < kMaxY ? H - h0 : kMaxY;
+    // steps cut to what is left, so that no index passes B or H (up to INT_MAX)
+    for (int b0 = 0, nb; b0 < B; b0 += nb) {
+        nb = B - b0 < step ? B - b0 : step;
+        for (int h0 = 0, nh; h0 < H; h0 += nh) {
+            nh = H - h0 < kMaxY ? H - h0 : kMaxY;
             const size_t at = (size_t)b0 * k * beam_bytes + (size_t)h0 * head_bytes;
             const dim3 gd(nblk, (unsigned)nh, (unsigned)(nb * tensors)), bd(kThreads);
             auto launch = [&](auto kernel) {
