@@ -1044,7 +1044,7 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
         // rows (find), then its rows' loads go out (fetch).
         Rows rows;
         typename TO::Q qo;
-        int own[kIt];
+        int own[kIt] = {};   // (fetch reads it for prefix tasks too, times a stride of 0)
         int t0 = 0, j1 = 0;
         bool gen = false;
         auto find = [&](int task) {
