@@ -962,10 +962,12 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
     using TO = OwnTile<D, BF16, KB>;
     constexpr bool kOwnIsTile = std::is_same<TL, TO>::value;
     constexpr int kTile = G::kTile, kLpr = G::kLpr, kRpi = G::kRpi;
-    // Rows of the next round on their way during this round's fold.  Where the
-    // registers for it (124, four waves per SIMD) are there: with D = 128, the
-    // VALU tile or generated tokens it costs a wave per SIMD.
-    constexpr bool kAhead = BF16 && (D == 32 || D == 64) && !GEN;
+    // Rows of the next round on their way during this round's fold.  Where
+    // there is a next round (the size rule gives four waves one round of prefix
+    // tiles) and the registers for it (D = 64: 124, four waves per SIMD) are
+    // there: with D = 128, the VALU tile or generated tokens it costs a wave
+    // per SIMD, with D = 32 and 16 waves it spills.
+    constexpr bool kAhead = BF16 && (D == 64 || (D == 32 && KW < 16)) && !GEN && KW > kWaves;
     constexpr int kThreads = KW * kWave, kPer = (KB * D + kThreads - 1) / kThreads;
     constexpr int kBatch = kWave;   // generated tiles whose sharing one ballot holds
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = wave_id();
