@@ -371,6 +371,13 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Orders this wave's LDS accesses before and after it.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // State of one wave tile: keys [t0, min(t0 + kTile, j1)), rows kr/vr (t0 <
 // j1), attended by the KB queries qr.  On return m[i], l[i] (base-2 max and
 // sum of exp2) are wave-uniform and acc[i][e] holds, in every lane, the
@@ -490,49 +497,88 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x8_t __attribute__((ext_vector_type(8)));
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
 
-template <int D, bool BF16, int KB>
+template <int D, bool BF16, int KB, int NG>
 struct ValuTile {
     using G = Geo<D, BF16>;
     static constexpr int kEpl = G::kEpl, kLpr = G::kLpr;
-    static constexpr int kLdsBytes = G::kPStride * KB * 4;  // per wave
-    struct Q { uint4 r[KB]; };
+    // NG < KB: NG beams are attended at a time, over the tile's rows in
+    // registers, with the queries in LDS (a beam's arithmetic is the same).
+    static constexpr bool kGroups = NG < KB;
     static constexpr int kAStride = D;  // floats between the beams of a wave's state in LDS
+    // a wave's LDS: the accumulators of its state, a tile's weights from
+    // kScratch on (groups: behind the accumulators of the groups before), its queries
+    static constexpr int kScratch = kGroups ? KB * kAStride * 4 : 0;
+    static constexpr int kTileBytes = G::kPStride * NG * 4;
+    static constexpr int kQBytes = kGroups ? KB * D * Elem<BF16>::size : 0;
+    struct Q {
+        uint4 r[kGroups ? 1 : KB];
+        const uint4 *lds;
+    };
     // m, l wave-uniform; acc[i][e] holds dims sub*kEpl + e in every lane
-    struct St { float m[KB], l[KB], acc[KB][kEpl]; };
+    struct St { float m[NG], l[NG], acc[NG][kEpl]; };
 
-    // queries of hypotheses hyp0 .. hyp0 + KB - 1, head h
+    // queries of hypotheses hyp0 .. hyp0 + KB - 1, head h; q_lds: kQBytes of this wave's LDS
     static __device__ __forceinline__ void load_q(Q &q, const uint4 *__restrict__ qp, size_t hyp0, int h, int H,
-                                                  int lane) {
+                                                  int lane, void *q_lds = nullptr) {
         const int sub = lane % kLpr;
+        if constexpr (kGroups) {
+            uint4 *to = static_cast<uint4 *>(q_lds);
+            uint4 r[KB];
 #pragma unroll
-        for (int i = 0; i < KB; ++i) q.r[i] = qp[((hyp0 + i) * H + h) * kLpr + sub];
-    }
-    static __device__ __forceinline__ void init(St &s) {
+            for (int i = 0; i < KB; ++i) r[i] = qp[((hyp0 + i) * H + h) * kLpr + sub];
+            if (lane < kLpr) {
 #pragma unroll
-        for (int i = 0; i < KB; ++i) {
-            s.m[i] = -INFINITY;
-            s.l[i] = 0.f;
+                for (int i = 0; i < KB; ++i) to[i * kLpr + lane] = r[i];
+            }
+            wave_lds_fence();
+            q.lds = to;
+        } else {
 #pragma unroll
-            for (int e = 0; e < kEpl; ++e) s.acc[i][e] = 0.f;
+            for (int i = 0; i < KB; ++i) q.r[i] = qp[((hyp0 + i) * H + h) * kLpr + sub];
         }
     }
     static __device__ __forceinline__ void attend(const Q &q, const Rows &r, int t0, int j1, int lane, void *lds,
                                                   float scale_log2, St &s) {
+        static_assert(!kGroups, "the state is that of one group");
         tile_attend<D, BF16, KB>(q.r, r.k, r.v, t0, j1, lane % kLpr, lane / kLpr, static_cast<float *>(lds),
                                  scale_log2, s.m, s.l, s.acc);
     }
     // this wave's state into LDS: m_w and l_w (beam i at i * ms), a_w[KB][kAStride]
     static __device__ __forceinline__ void to_lds(const St &s, int lane, float *m_w, float *l_w, int ms, float *a_w) {
+        put<NG>(s, lane, m_w, l_w, ms, a_w);
+    }
+    // attend and to_lds group by group
+    template <int I0 = 0>
+    static __device__ __forceinline__ void attend_groups(const Q &q, const Rows &r, int t0, int j1, int lane,
+                                                         void *lds, float scale_log2, float *m_w, float *l_w, int ms,
+                                                         float *a_w) {
+        constexpr int N = KB - I0 < NG ? KB - I0 : NG;
+        uint4 qr[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) qr[i] = q.lds[(I0 + i) * kLpr + lane % kLpr];
+        typename ValuTile<D, BF16, N, N>::St s;
+        tile_attend<D, BF16, N>(qr, r.k, r.v, t0, j1, lane % kLpr, lane / kLpr, static_cast<float *>(lds), scale_log2,
+                                s.m, s.l, s.acc);
+        put<N>(s, lane, m_w + I0 * ms, l_w + I0 * ms, ms, a_w + I0 * kAStride);
+        if constexpr (I0 + N < KB) {
+            __builtin_amdgcn_sched_barrier(0);   // the next group takes this one's registers
+            attend_groups<I0 + N>(q, r, t0, j1, lane, lds, scale_log2, m_w, l_w, ms, a_w);
+        }
+    }
+
+private:
+    template <int N, class S>
+    static __device__ __forceinline__ void put(const S &s, int lane, float *m_w, float *l_w, int ms, float *a_w) {
         if (lane < kLpr) {
 #pragma unroll
-            for (int i = 0; i < KB; ++i) {
+            for (int i = 0; i < N; ++i) {
 #pragma unroll
                 for (int e = 0; e < kEpl; ++e) a_w[i * kAStride + lane * kEpl + e] = s.acc[i][e];
             }
         }
         if (lane == 0) {
 #pragma unroll
-            for (int i = 0; i < KB; ++i) {
+            for (int i = 0; i < N; ++i) {
                 m_w[i * ms] = s.m[i];
                 l_w[i * ms] = s.l[i];
             }
@@ -596,7 +642,9 @@ struct MfmaTile {
     static constexpr int NS = D / 32;     // 32-dim steps of QK^T
     static constexpr int NU = D / 16;     // 32-byte units per row = 16-dim output blocks
     static constexpr int kLpr = D / 8;    // 16-byte slices per row
-    static constexpr int kLdsBytes = T * D * 2;  // one tile of rows (8 KB): K, then V
+    // a wave's LDS: one tile of rows (8 KB), K, then V, then the accumulators in its place
+    static constexpr bool kGroups = false;
+    static constexpr int kScratch = 0, kTileBytes = T * D * 2, kQBytes = 0;
     static_assert(D == 32 || D == 64 || D == 128, "MFMA tile needs D in {32, 64, 128}");
     static_assert(KB <= 16, "beams are the 16 columns of the MFMA");
     static_assert(NKB % 2 == 0, "PV takes 32 keys per instruction");
@@ -616,7 +664,7 @@ struct MfmaTile {
         return c ^ ((r >> sh) & (NU - 1));
     }
     static __device__ __forceinline__ void load_q(Q &q, const uint4 *__restrict__ qp, size_t hyp0, int h, int H,
-                                                  int lane) {
+                                                  int lane, void * = nullptr) {
         const int n = lane & 15, g = lane >> 4;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
@@ -624,12 +672,6 @@ struct MfmaTile {
             if (n < KB) v = qp[((hyp0 + n) * H + h) * kLpr + 4 * s + g];
             q.b[s] = __builtin_bit_cast(bf16x8_t, v);
         }
-    }
-    static __device__ __forceinline__ void init(St &s) {
-        s.m = -INFINITY;
-        s.l = 0.f;
-#pragma unroll
-        for (int mb = 0; mb < NU; ++mb) s.acc[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
     // row r of the tile (2 D bytes), 16-byte slice sl, in the swizzled LDS tile
     static __device__ __forceinline__ int lds_off(int r, int sl) {
@@ -743,23 +785,41 @@ struct MfmaTile {
     }
 };
 
-template <int D, bool BF16, int KB>
-using Tile = typename std::conditional<(BF16 && D >= 32), MfmaTile<D, KB>, ValuTile<D, BF16, KB>>::type;
+// Beams the VALU tile attends at a time in a workgroup of KW waves (0: the
+// kernel of one chunk per workgroup, whose waves attend one tile each: all at
+// once).  Its registers grow with the beams (eight: 146 without generated
+// tokens, 185 with, and scratch in sixteen waves' 128), so from seven on, with
+// generated tokens from six, they go in groups (104 and 143).  fp32, 8 beams,
+// 192 rows of 700 keys: D = 64 24.2 us with all at once, 18.6 in groups of 4;
+// 640 rows of 300 + 20: 46.0 and 33.5.  Pairs cost time where few rows leave
+// each wave's chain of groups exposed (64 rows of 200 + 30: 8.6 us against 7.3).
+constexpr int valu_group(bool bf16, int KB, bool gen, int KW) {
+    if (KW == 0) return KB;
+    if (gen) return KB < 6 ? KB : 2;
+    return KB < 7 || bf16 ? KB : KB == 8 ? 4 : KW == 8 ? 2 : KB;
+}
+template <int D, bool BF16, int KB, bool GEN, int KW>
+using Tile = typename std::conditional<(BF16 && D >= 32), MfmaTile<D, KB>,
+                                       ValuTile<D, BF16, KB, valu_group(BF16, KB, GEN, KW)>>::type;
 
 // Tile policy of a generated-token tile that belongs to one beam.  The matrix
 // cores take the beam as one of the KB columns at no extra cost (only its
 // column is used); the VALU tile attends it alone.
 template <int D, bool BF16, int KB>
-using OwnTile = typename std::conditional<(BF16 && D >= 32), MfmaTile<D, KB>, ValuTile<D, BF16, 1>>::type;
+using OwnTile = typename std::conditional<(BF16 && D >= 32), MfmaTile<D, KB>, ValuTile<D, BF16, 1, 1>>::type;
 
-// LDS area of one wave: large enough for a tile of KB beams or of one beam,
-// and for the wave's acc (KB rows of kAStride floats) once its tile is done;
-// a 16-byte multiple.
-template <int D, bool BF16, int KB>
+// LDS area of one wave: its state's accumulators (KB rows of kAStride floats),
+// the scratch of a tile of KB beams or of one beam from kScratch on, and its
+// queries; 16-byte multiples.
+template <int D, bool BF16, int KB, bool GEN, int KW>
 struct WaveLds {
-    static constexpr int a = Tile<D, BF16, KB>::kLdsBytes, b = OwnTile<D, BF16, KB>::kLdsBytes;
-    static constexpr int c = KB * Tile<D, BF16, KB>::kAStride * 4;
-    static constexpr int kBytes = ((a > b ? (a > c ? a : c) : (b > c ? b : c)) + 15) / 16 * 16;
+    using TL = Tile<D, BF16, KB, GEN, KW>;
+    using TC = Tile<D, BF16, KB, GEN, 0>;   // of the kernel of one chunk (KW = kWaves)
+    static constexpr int a = TL::kTileBytes, b = OwnTile<D, BF16, KB>::kTileBytes;
+    static constexpr int c0 = KB * TL::kAStride * 4, c1 = KW == kWaves ? TC::kTileBytes : 0;
+    static constexpr int c = c0 > c1 ? c0 : c1, d = TL::kScratch + (a > b ? a : b);
+    static constexpr int kQ = ((c > d ? c : d) + 15) / 16 * 16;   // offset of the queries
+    static constexpr int kBytes = kQ + TL::kQBytes;
 };
 
 // What the kWaves waves from w0 on left in LDS for output (beam i, dim d):
@@ -903,15 +963,19 @@ struct GenRows {
 // generated tiles the beam its task belongs to (-1: every beam) and, with an
 // ancestry table (ANC), per tile of a batch whether the beams share it and the
 // owners of its rows if so.
-template <int D, bool BF16, int KB, int KW, bool ANC>
+template <int D, bool BF16, int KB, int KW, bool GEN, bool ANC, bool BM>
 struct RowLds {
     __attribute__((aligned(16))) float m[KB][KW], l[KB][KW];
-    __attribute__((aligned(16))) char t[KW][WaveLds<D, BF16, KB>::kBytes];
+    __attribute__((aligned(16))) char t[KW][WaveLds<D, BF16, KB, GEN, KW>::kBytes];
     int task[KW];
     // (tiles of more rows, D = 16 and 32 in bf16, would not fit beside 16 waves)
-    static constexpr bool kOwners = ANC && Geo<D, BF16>::kTile <= kWave;
+    static constexpr bool kOwners = ANC && !BM && Geo<D, BF16>::kTile <= kWave;
     unsigned char shared[kWave], owner[kOwners ? kWave : 1][Geo<D, BF16>::kTile];
+    // generated tokens' states, where a wave walks a beam's (BM)
+    float gm[BM ? KB : 1], gl[BM ? KB : 1], ga[BM ? KB : 1][D];
     __device__ __forceinline__ float *acc(int w) { return reinterpret_cast<float *>(&t[w][0]); }
+    __device__ __forceinline__ void *scratch(int w) { return &t[w][Tile<D, BF16, KB, GEN, KW>::kScratch]; }
+    __device__ __forceinline__ void *queries(int w) { return &t[w][WaveLds<D, BF16, KB, GEN, KW>::kQ]; }
 };
 
 // Running softmax state of a thread's outputs x = tid + p * threads (beam
@@ -929,6 +993,80 @@ struct OutState {
     }
 };
 
+// Generated tokens of the row's beams w, w + gw, ... (this wave's), each over
+// its tiles in order, into lds.gm, gl and ga.  Through a table the owners of the
+// next tile's rows are read while a tile's rows are on their way.
+template <int D, bool BF16, int KB, int KW, bool ANC>
+__device__ __forceinline__ void generated_beams(RowLds<D, BF16, KB, KW, true, ANC, true> &lds,
+                                                const uint4 *__restrict__ q, int w, int gw, int b, int h, int H,
+                                                const GenRows &gr, float scale_log2)
+{
+    using TO = OwnTile<D, BF16, KB>;
+    using G = Geo<D, BF16>;
+    constexpr int kTile = G::kTile, kLpr = G::kLpr, kRpi = G::kRpi, kRow = kLpr * 16;
+    const int lane = threadIdx.x & (kWave - 1);
+    const size_t hyp0 = (size_t)b * KB;
+    for (int i = w; i < KB; i += gw) {
+        typename TO::Q qo;
+        TO::load_q(qo, q, hyp0 + i, h, H, lane);
+        // read through the table: from the source's beam-0 block on
+        const size_t base = ((ANC ? hyp0 : hyp0 + i) * H + h) * (size_t)gr.T * kLpr;
+        constexpr int kE = (D + kWave - 1) / kWave;
+        float gm = -INFINITY, gl = 0.f, ga[kE];   // ga[e]: of dim (e * kWave + lane) % D
+#pragma unroll
+        for (int e = 0; e < kE; ++e) ga[e] = 0.f;
+        int own[kIt] = {};   // owners of the next tile's rows, on their way during this one
+        auto look = [&](int t0) {
+            if constexpr (ANC) {
+                const int32_t *row = gr.anc + (hyp0 + i) * gr.ld;
+#pragma unroll
+                for (int u = 0; u < kIt; ++u) own[u] = row[min(t0 + u * kRpi + lane / kLpr, gr.t - 1)];
+            }
+        };
+        look(0);
+        for (int t0 = 0; t0 < gr.t; t0 += kTile) {
+            Rows rows;
+            if constexpr (ANC) {
+                const int stride = H * gr.T * kRow;   // bytes between two beams' blocks
+                int off[kIt];
+#pragma unroll
+                for (int u = 0; u < kIt; ++u) {
+                    const int j = t0 + u * kRpi + lane / kLpr;
+                    const int o = (own[u] >= 0 && own[u] < KB) ? own[u] : i;
+                    const int at = o * stride + j * kRow + lane % kLpr * 16;
+                    off[u] = j < gr.t ? at : 0x7ffffff0;   // past the range: zero, no access
+                }
+                load_tile_at(rows, gr.Kt + base, gr.Vt + base, KB * stride, off);
+                look(min(t0 + kTile, gr.t - 1));
+            } else {
+                load_tile<D, BF16, false>(rows, gr.Kt + base, gr.Vt + base, t0, gr.t, lane);
+            }
+            typename TO::St st;
+            TO::attend(qo, rows, t0, gr.t, lane, lds.scratch(w), scale_log2, st);
+            TO::to_lds(st, lane, &lds.m[0][w], &lds.l[0][w], KW, lds.acc(w));
+            wave_lds_fence();
+            const float tm = lds.m[0][w], tl = lds.l[0][w];
+#pragma unroll
+            for (int e = 0; e < kE; ++e) {
+                float m = gm, l = gl;   // the same for every dim
+                merge_state(m, l, ga[e], tm, tl, lds.acc(w)[(e * kWave + lane) % D]);
+                if (e == kE - 1) {
+                    gm = m;
+                    gl = l;
+                }
+            }
+            wave_lds_fence();
+        }
+#pragma unroll
+        for (int e = 0; e < kE; ++e)
+            if (e * kWave + lane < D) lds.ga[i][e * kWave + lane] = ga[e];
+        if (lane == 0) {
+            lds.gm[i] = gm;
+            lds.gl[i] = gl;
+        }
+    }
+}
+
 // One (source, head) row walked by the KW waves of a workgroup in rounds of
 // KW tile tasks, one task per wave: the npt tiles of the prefix (Kbh/Vbh, L
 // keys), then with GEN the tiles of the generated tokens.  R receives the
@@ -942,15 +1080,19 @@ struct OutState {
 // one task for all of them, read once like a prefix tile.  The split cache
 // with 512 generated rows and 5 beams (512 rows of 75 to 300 prefix keys)
 // took 72 us when the first four waves walked each beam's tiles in turn; the
-// tasks spread over all waves take 23 us.
+// tasks spread over all waves take 23 us.  With BM (beam_waves) the first waves
+// do walk each beam's tiles, in the place of the round's first tasks: the VALU
+// tile of a beam and that of all beams do not share a loop then, which in one
+// cost up to 80 registers more.
 //
 // The latest generated tile is one task per beam in any case (each beam's
 // last token is its own).  Its tasks go first, beside the first prefix tiles:
 // its rows lie in k separate blocks of memory, which a last round of a few
 // waves reads slowly (192 rows of up to 1024 prefix keys, 64 generated, k = 4:
 // 12.0 us, against 12.2 us with every generated tile after the prefix).
-template <int D, bool BF16, int KB, int KW, bool GEN, bool ANC>
-__device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, const typename Tile<D, BF16, KB>::Q &qv,
+template <int D, bool BF16, int KB, int KW, bool GEN, bool ANC, bool BM>
+__device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, GEN, ANC, BM> &lds,
+                                         const typename Tile<D, BF16, KB, GEN, KW>::Q &qv,
                                          const uint4 *__restrict__ q, const uint4 *__restrict__ Kbh,
                                          const uint4 *__restrict__ Vbh, int L, int b, int h, int H, const GenRows &gr,
                                          float scale_log2, OutState<(KB * D + KW * kWave - 1) / (KW * kWave)> &R,
@@ -958,8 +1100,9 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
                                          unsigned long long *trs)
 {
     using G = Geo<D, BF16>;
-    using TL = Tile<D, BF16, KB>;
+    using TL = Tile<D, BF16, KB, GEN, KW>;
     using TO = OwnTile<D, BF16, KB>;
+    using Lds = RowLds<D, BF16, KB, KW, GEN, ANC, BM>;
     constexpr bool kOwnIsTile = std::is_same<TL, TO>::value;
     constexpr int kTile = G::kTile, kLpr = G::kLpr, kRpi = G::kRpi;
     // Rows of the next round on their way during this round's fold.  Where
@@ -972,15 +1115,28 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
     constexpr int kBatch = kWave;   // generated tiles whose sharing one ballot holds
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = wave_id();
     const int npt = (L + kTile - 1) / kTile;
-    const int ngt = GEN ? (gr.t + kTile - 1) / kTile : 0;
+    const int ngt = GEN && !BM ? (gr.t + kTile - 1) / kTile : 0;
     const size_t hyp0 = (size_t)b * KB;
     float *const m_w = &lds.m[0][w], *const l_w = &lds.l[0][w];   // beam i at i * KW
 
+    // Early tasks (below) keep their states in registers, which the VALU tile
+    // has for D = 16 and for five beams without a table only.
+    constexpr bool kEarly = GEN && KB >= kWaves && !BM && ((BF16 && D >= 32) || D == 16 || (KB == 5 && !ANC));
+    // waves that walk beams in the place of the first tasks (a multiple of
+    // kWaves): one per beam, but half as many of eight where the others take
+    // the whole prefix meanwhile
+    int beams = 0;
+    if constexpr (BM) {
+        if (gr.t > 0) beams = kWaves;
+        if (KB > kWaves && KW > kWaves &&
+            (KW > 2 * kWaves || npt == 0 || npt > KW - kWaves || gr.t > 2 * kTile)) beams *= 2;
+        if (w < beams) generated_beams<D, BF16, KB, KW, ANC>(lds, q, w, beams, b, h, H, gr, scale_log2);
+    }
     R.init();
     OutState<kPer> last;   // the early tasks' states, folded at the end
     if constexpr (GEN) {
         Gs.init();
-        last.init();
+        if constexpr (kEarly) last.init();
     }
 
     // owner of generated row j of beam i, in [0, KB)
@@ -991,10 +1147,10 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
         const int ng = min(kBatch, ngt - gb);
         // the tasks before the prefix: beams 0 .. early - 1 of the last tile
         // (a multiple of kWaves, so that the prefix's chunks stay aligned)
-        const int early = GEN && ng > 0 && ngt <= kBatch ? KB / kWaves * kWaves : 0;
+        const int early = BM ? beams : kEarly && ng > 0 && ngt <= kBatch ? KB / kWaves * kWaves : 0;
         const int pre1 = early + npre;   // end of the prefix tasks
         unsigned long long sh = 0;      // tiles of the batch with one owner per row for every beam
-        int ntask = npre + ng * KB;
+        int ntask = BM ? pre1 : npre + ng * KB;
         // Does tile jt of the batch have one owner per row?  (one wave per
         // tile, which leaves the owners in LDS)
         auto mark_shared = [&]() {
@@ -1008,7 +1164,7 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
                     for (int i = 0; i < KB; ++i) a[i] = col[(size_t)i * gr.ld];
 #pragma unroll
                     for (int i = 1; i < KB; ++i) same &= owner(a[i], i) == owner(a[0], 0);
-                    if (RowLds<D, BF16, KB, KW, ANC>::kOwners) lds.owner[jt][p] = (unsigned char)owner(a[0], 0);
+                    if (Lds::kOwners) lds.owner[jt][p] = (unsigned char)owner(a[0], 0);
                 }
                 const bool all = __builtin_amdgcn_ballot_w64(!same) == 0ull;
                 if (lane == 0) lds.shared[jt] = all;
@@ -1050,7 +1206,7 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
         int t0 = 0, j1 = 0;
         bool gen = false;
         auto find = [&](int task) {
-            gen = GEN && (task < early || task >= pre1);
+            gen = GEN && !BM && (task < early || task >= pre1);
             t0 = (task - early) * kTile;
             j1 = task < ntask ? L : 0;   // no task: loads of an empty range
             if (!gen || task >= ntask) return;
@@ -1058,7 +1214,7 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
             t0 = (gb + g_tile) * kTile;
             j1 = gr.t;
             if constexpr (ANC) {
-                if (RowLds<D, BF16, KB, KW, ANC>::kOwners && g_beam < 0) {
+                if (Lds::kOwners && g_beam < 0) {
 #pragma unroll
                     for (int u = 0; u < kIt; ++u) own[u] = lds.owner[g_tile][u * kRpi + lane / kLpr];
                 } else {
@@ -1112,20 +1268,24 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
         if constexpr (kAhead) fetch();
         for (int q0 = 0; q0 < ntask; q0 += KW) {
             const int task = q0 + w;
-            if (task < ntask) {
-                if constexpr (GEN) {
+            if (task < ntask && !(BM && task < early)) {
+                if constexpr (GEN && !BM) {
                     if (gen && lane == 0) lds.task[w] = g_beam;
                 }
                 // the loads beside their use: the VALU tile takes its V rows late
-                if (kOwnIsTile || !gen || g_beam < 0) {
-                    typename TL::St st;
+                if (kOwnIsTile || BM || !gen || g_beam < 0) {
                     if constexpr (!kAhead) fetch();
-                    TL::attend(qv, rows, t0, j1, lane, &lds.t[w][0], scale_log2, st);
-                    TL::to_lds(st, lane, m_w, l_w, KW, lds.acc(w));
+                    if constexpr (TL::kGroups) {
+                        TL::attend_groups(qv, rows, t0, j1, lane, lds.scratch(w), scale_log2, m_w, l_w, KW, lds.acc(w));
+                    } else {
+                        typename TL::St st;
+                        TL::attend(qv, rows, t0, j1, lane, &lds.t[w][0], scale_log2, st);
+                        TL::to_lds(st, lane, m_w, l_w, KW, lds.acc(w));
+                    }
                 } else if constexpr (!kOwnIsTile) {
                     typename TO::St st;
                     fetch();
-                    TO::attend(qo, rows, t0, j1, lane, &lds.t[w][0], scale_log2, st);
+                    TO::attend(qo, rows, t0, j1, lane, lds.scratch(w), scale_log2, st);
                     TO::to_lds(st, lane, m_w + g_beam * KW, l_w + g_beam * KW, KW, lds.acc(w) + g_beam * TL::kAStride);
                 }
             }
@@ -1151,7 +1311,14 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
                 const int x = tid + p * kThreads;
                 if (x < KB * D) {
                     const int i = x / D, d = x - i * D;
-                    if constexpr (GEN) {
+                    if constexpr (BM) {
+                        if (q0 == 0 && beams) {
+                            Gs.m[p] = lds.gm[i];
+                            Gs.l[p] = lds.gl[i];
+                            Gs.a[p] = lds.ga[i][d];
+                        }
+                    }
+                    if constexpr (kEarly) {
                         const int we = i - q0;   // the wave of beam i's early task
                         if (q0 < early && i < early && we >= 0 && we < KW) {
                             last.m[p] = lds.m[i][we];
@@ -1170,7 +1337,7 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
                             merge_state(R.m[p], R.l[p], R.a[p], cm, cl, ca);
                         }
                     }
-                    if constexpr (GEN) {
+                    if constexpr (GEN && !BM) {
                         // generated tiles, those of this beam, in order
                         for (int ww = max(pre1 - q0, 0); ww < min(KW, ntask - q0); ++ww) {
                             const int tb = __builtin_amdgcn_readfirstlane(lds.task[ww]);
@@ -1185,7 +1352,7 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
             if (gb == 0 && q0 == 0) trace::stamp(trs, 5);
         }
     }
-    if constexpr (GEN && KB >= kWaves) {
+    if constexpr (kEarly) {
 #pragma unroll
         for (int p = 0; p < kPer; ++p) merge_state(Gs.m[p], Gs.l[p], Gs.a[p], last.m[p], last.l[p], last.a[p]);
     }
@@ -1193,14 +1360,15 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, ANC> &lds, cons
 
 // Generated-token segment of (b, h) = bh (SPLIT only): its state goes to
 // record slot NT of (b, h).
-template <int D, bool BF16, int KB, bool ANC>
-__device__ __forceinline__ void attend_generated(RowLds<D, BF16, KB, kWaves, ANC> &lds, const uint4 *__restrict__ q,
+template <int D, bool BF16, int KB, bool ANC, bool BM>
+__device__ __forceinline__ void attend_generated(RowLds<D, BF16, KB, kWaves, true, ANC, BM> &lds,
+                                                 const uint4 *__restrict__ q,
                                                  unsigned long long *__restrict__ part, int bh, int n_bh, int H,
                                                  Div by_H, int NT, const GenRows &gr, float scale_log2,
                                                  unsigned long long epoch,
                                                  const unsigned long long *__restrict__ ctr)
 {
-    using TL = Tile<D, BF16, KB>;
+    using TL = Tile<D, BF16, KB, true, kWaves>;
     constexpr int kPer = (KB * D + kBlock - 1) / kBlock;
     if (bh >= n_bh || gr.t <= 0) return;
     const int b = by_H(bh);
@@ -1209,9 +1377,10 @@ __device__ __forceinline__ void attend_generated(RowLds<D, BF16, KB, kWaves, ANC
     unsigned long long c0;
     const unsigned long long tag = call_tag(epoch, ctr + bh, c0);
     typename TL::Q qv;
-    TL::load_q(qv, q, (size_t)b * KB, h, H, threadIdx.x & (kWave - 1));
+    TL::load_q(qv, q, (size_t)b * KB, h, H, threadIdx.x & (kWave - 1), lds.queries(wave_id()));
     OutState<kPer> R, Gs;
-    walk_row<D, BF16, KB, kWaves, true, ANC>(lds, qv, q, nullptr, nullptr, 0, b, h, H, gr, scale_log2, R, Gs, nullptr);
+    walk_row<D, BF16, KB, kWaves, true, ANC, BM>(lds, qv, q, nullptr, nullptr, 0, b, h, H, gr, scale_log2, R, Gs,
+                                                 nullptr);
     unsigned long long *rec = part + ((size_t)bh * (NT + 1) + NT) * kRec;
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
@@ -1226,7 +1395,7 @@ __device__ __forceinline__ void attend_generated(RowLds<D, BF16, KB, kWaves, ANC
     }
 }
 
-template <int D, bool BF16, int KB, bool SPLIT, bool ANC = false>
+template <int D, bool BF16, int KB, bool SPLIT, bool ANC, bool BM>
 __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     const uint4 *__restrict__ q, const uint4 *__restrict__ K, const uint4 *__restrict__ V,
     const int32_t *__restrict__ src_len, int ng_blocks, int n_bh, int H, unsigned h_mul, int h_shift, int NC, int S,
@@ -1237,7 +1406,7 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     int ld_anc, NgramJob ngj)
 {
     using G = Geo<D, BF16>;
-    using TL = Tile<D, BF16, KB>;
+    using TL = Tile<D, BF16, KB, SPLIT, 0>;
     constexpr int kLpr = G::kLpr;
     constexpr int kTile = G::kTile, kChunk = G::kChunk;
 
@@ -1249,7 +1418,7 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
         return;
     }
 
-    __shared__ RowLds<D, BF16, KB, kWaves, ANC> lds;
+    __shared__ RowLds<D, BF16, KB, kWaves, SPLIT, ANC, BM> lds;
 
     // Workgroup g runs on XCD g % 8 (round-robin dispatch).  All chunks of
     // one (b, h), its generated-token workgroup and its merger get ids with
@@ -1260,7 +1429,7 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
     int g = blockIdx.x - ng_blocks;
     if constexpr (SPLIT) {
         if (g < n_bh8) {
-            attend_generated<D, BF16, KB, ANC>(lds, q, part, g, n_bh, H, by_H, NC * kWaves,
+            attend_generated<D, BF16, KB, ANC, BM>(lds, q, part, g, n_bh, H, by_H, NC * kWaves,
                                                GenRows{Kt, Vt, T, t, anc, ld_anc}, scale_log2, epoch, ctr);
             return;
         }
@@ -1342,7 +1511,7 @@ __global__ __launch_bounds__(kBlock) void cross_attn_kernel(
 // combined, the chunk states folded in chunk order from the empty state, the
 // generated-token state last -- so both kernels give the same bits.  It pays
 // when there are enough (b, h) rows to fill the chip without splitting them.
-template <int D, bool BF16, int KB, bool SPLIT, int P, bool ANC = false>
+template <int D, bool BF16, int KB, bool SPLIT, int P, bool ANC, bool BM>
 __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
     const uint4 *__restrict__ q, const uint4 *__restrict__ K, const uint4 *__restrict__ V,
     const int32_t *__restrict__ src_len, int ng_blocks, int H, unsigned h_mul, int h_shift, int S, float scale_log2,
@@ -1350,13 +1519,13 @@ __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
     const int32_t *__restrict__ anc, int ld_anc, NgramJob ngj)
 {
     using G = Geo<D, BF16>;
-    using TL = Tile<D, BF16, KB>;
     constexpr int kLpr = G::kLpr;
     constexpr int kW = kWaves * P;                        // waves per workgroup
+    using TL = Tile<D, BF16, KB, SPLIT, kW>;
     constexpr int kThreads = kBlock * P;
     constexpr int kPer = (KB * D + kThreads - 1) / kThreads;  // outputs per thread
 
-    __shared__ RowLds<D, BF16, KB, kW, ANC> lds;
+    __shared__ RowLds<D, BF16, KB, kW, SPLIT, ANC, BM> lds;
 
     const Div by_H{h_mul, h_shift};
     // A fused decode step's n-gram rows take the first workgroups.
@@ -1375,10 +1544,10 @@ __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
     const int tid = threadIdx.x;
     const size_t obase = ((size_t)b * KB * H + h) * D;  // out[b, 0, h, 0]
     typename TL::Q qv;
-    TL::load_q(qv, q, (size_t)b * KB, h, H, tid & (kWave - 1));
+    TL::load_q(qv, q, (size_t)b * KB, h, H, tid & (kWave - 1), lds.queries(wave_id()));
     OutState<kPer> R, Gs;
-    walk_row<D, BF16, KB, kW, SPLIT, ANC>(lds, qv, q, K + (size_t)bh * S * kLpr, V + (size_t)bh * S * kLpr, L, b, h, H,
-                                          GenRows{Kt, Vt, T, t, anc, ld_anc}, scale_log2, R, Gs, trs);
+    walk_row<D, BF16, KB, kW, SPLIT, ANC, BM>(lds, qv, q, K + (size_t)bh * S * kLpr, V + (size_t)bh * S * kLpr, L, b, h,
+                                              H, GenRows{Kt, Vt, T, t, anc, ld_anc}, scale_log2, R, Gs, trs);
     if constexpr (SPLIT) {
         if (t > 0) {
 #pragma unroll
@@ -1403,6 +1572,23 @@ __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
 
 }  // namespace
 
+// Whether a wave walks a beam's generated tokens by itself (only where the
+// VALU tile attends them; the matrix-core tile's tasks spread over all waves).
+// Without a table every beam's rows are read in any case, and the loop of tasks
+// costs the registers of two tiles.  Through one, tasks read what the beams
+// share once, which pays from the second tile on; a beam's wave saves them the
+// look at the table (us, fp32, D = 64, k = 8, S = 300 keys, n rows, t tokens,
+// beams' waves against tasks: n = 256, t = 20: 19 / 23; n = 128, t = 150: 25 /
+// 25; n = 640, t = 500: 128 / 91).
+inline bool beam_waves(int n_bh, int D, int esize, int k, int nt, int t, bool table) {
+    if (esize == 2 && D >= 32) return false;
+    if (!table) return D == 16 ? k >= 3 : k == 4 || k >= 6;
+    if (k < (D == 16 ? 3 : 4)) return false;
+    const int tile = kIt * kWave * 16 / (D * esize);
+    const bool few = n_bh <= kCus || (nt == 0 && D > 16 && k >= 6);
+    return t <= tile * (!few ? 1 : k >= 6 ? 3 : D == 16 && esize == 2 ? 2 : 1);
+}
+
 // Launch arguments shared by both entry points.  For the encoder-decoder
 // form Kt/Vt are null and T = t = 0.
 struct AttnArgs {
@@ -1419,11 +1605,12 @@ struct AttnArgs {
     hipStream_t stream;
     NgramJob ng;          // n-gram rows of a fused decode step (ng.rows == 0: none)
     AttnPath path;        // decomposition chosen for the call
+    bool beams;           // generated tokens through a table by beam_waves
 };
 
 namespace {
 
-template <int D, bool BF16, int KB, bool SPLIT, bool ANC = false>
+template <int D, bool BF16, int KB, bool SPLIT, bool ANC, bool BM>
 hipError_t launch_split(const AttnArgs &a, int NC)
 {
     const int n_bh = a.B * a.H;
@@ -1441,7 +1628,7 @@ hipError_t launch_split(const AttnArgs &a, int NC)
     ng.blocks = (ng.blocks + kXcds - 1) / kXcds * kXcds;
     const long long nblk = ng.blocks + (SPLIT ? n_bh8 : 0) + n_bh8 * NC + mergers;
     const Div dv = make_div(a.H);
-    hipLaunchKernelGGL((cross_attn_kernel<D, BF16, KB, SPLIT, ANC>), dim3((unsigned)nblk), dim3(kBlock), 0,
+    hipLaunchKernelGGL((cross_attn_kernel<D, BF16, KB, SPLIT, ANC, BM>), dim3((unsigned)nblk), dim3(kBlock), 0,
                        a.stream, static_cast<const uint4 *>(a.q), static_cast<const uint4 *>(a.K),
                        static_cast<const uint4 *>(a.V), a.src_len, ng.blocks, n_bh, a.H, dv.mul, dv.shift, NC, a.S,
                        (float)scale_log2, a.out, part, a.epoch, ctr, static_cast<const uint4 *>(a.Kt),
@@ -1449,7 +1636,7 @@ hipError_t launch_split(const AttnArgs &a, int NC)
     return hipGetLastError();
 }
 
-template <int D, bool BF16, int KB, bool SPLIT, int P, bool ANC = false>
+template <int D, bool BF16, int KB, bool SPLIT, int P, bool ANC, bool BM>
 hipError_t launch_whole(const AttnArgs &a)
 {
     const int n_bh = a.B * a.H;
@@ -1457,7 +1644,7 @@ hipError_t launch_whole(const AttnArgs &a)
     NgramJob ng = a.ng;
     ng.blocks = ng.rows > 0 ? (ng.rows + kWaves * P - 1) / (kWaves * P) : 0;
     const Div dv = make_div(a.H);
-    hipLaunchKernelGGL((attn_whole_kernel<D, BF16, KB, SPLIT, P, ANC>), dim3((unsigned)(ng.blocks + n_bh)),
+    hipLaunchKernelGGL((attn_whole_kernel<D, BF16, KB, SPLIT, P, ANC, BM>), dim3((unsigned)(ng.blocks + n_bh)),
                        dim3(kBlock * P), 0,
                        a.stream, static_cast<const uint4 *>(a.q), static_cast<const uint4 *>(a.K),
                        static_cast<const uint4 *>(a.V), a.src_len, ng.blocks, a.H, dv.mul, dv.shift, a.S,
@@ -1467,31 +1654,36 @@ hipError_t launch_whole(const AttnArgs &a)
     return hipGetLastError();
 }
 
+template <int D, bool BF16, int KB, bool SPLIT, bool ANC, bool BM>
+hipError_t launch_path(const AttnArgs &a)
+{
+    // at least one chunk column, so that a source with no valid key (or
+    // S == 0) still has a workgroup to write its zero output
+    constexpr int kChunk = Geo<D, BF16>::kChunk;
+    switch (a.path) {
+    case AttnPath::kWhole1: return launch_whole<D, BF16, KB, SPLIT, 1, ANC, BM>(a);
+    case AttnPath::kWhole2: return launch_whole<D, BF16, KB, SPLIT, 2, ANC, BM>(a);
+    case AttnPath::kWhole4: return launch_whole<D, BF16, KB, SPLIT, 4, ANC, BM>(a);
+    default: return launch_split<D, BF16, KB, SPLIT, ANC, BM>(a, max(1, (a.S + kChunk - 1) / kChunk));
+    }
+}
+
 template <int D, bool BF16, int KB, bool SPLIT>
 hipError_t launch_typed(const AttnArgs &a)
 {
-    using G = Geo<D, BF16>;
-    // at least one chunk column, so that a source with no valid key (or
-    // S == 0) still has a workgroup to write its zero output
-    const int NC = max(1, (a.S + G::kChunk - 1) / G::kChunk);
-    const AttnPath path = a.path;
     if constexpr (SPLIT) {
+        // Generated rows through the ancestry table: their own kernels, so that
+        // the table-free ones keep their registers.
+        constexpr bool kValu = !(BF16 && D >= 32);
         if (a.anc) {
-            // generated rows through the ancestry table: their own kernels,
-            // so that the table-free ones keep their registers
-            switch (path) {
-            case AttnPath::kWhole1: return launch_whole<D, BF16, KB, true, 1, true>(a);
-            case AttnPath::kWhole2: return launch_whole<D, BF16, KB, true, 2, true>(a);
-            case AttnPath::kWhole4: return launch_whole<D, BF16, KB, true, 4, true>(a);
-            default: return launch_split<D, BF16, KB, true, true>(a, NC);
+            if constexpr (kValu && KB >= (D == 16 ? 3 : 4)) {
+                if (a.beams) return launch_path<D, BF16, KB, true, true, true>(a);
             }
+            return launch_path<D, BF16, KB, true, true, false>(a);
         }
-    }
-    switch (path) {
-    case AttnPath::kWhole1: return launch_whole<D, BF16, KB, SPLIT, 1>(a);
-    case AttnPath::kWhole2: return launch_whole<D, BF16, KB, SPLIT, 2>(a);
-    case AttnPath::kWhole4: return launch_whole<D, BF16, KB, SPLIT, 4>(a);
-    default: return launch_split<D, BF16, KB, SPLIT>(a, NC);
+        return launch_path<D, BF16, KB, true, false, kValu && (D == 16 ? KB >= 3 : KB == 4 || KB >= 6)>(a);
+    } else {
+        return launch_path<D, BF16, KB, false, false, false>(a);
     }
 }
 
@@ -1596,6 +1788,36 @@ AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool 
     // The lines below were measured on MI355X over 16 to 1024 rows, 128 to 2048
     // keys, 0 to 500 generated tokens, D = 64 and 128, bf16 and f32 (graph
     // replays of three rotated inputs).
+    if ((esize == 4 || D == 16) && t > 0) {
+        // Generated tokens on the VALU tile (fp32, and D = 16).  More rows than
+        // CUs: four waves where eight have more than 128 registers (one
+        // workgroup per CU then), eight where the prefix is long beside what is
+        // generated (us, fp32, D = 64, 4 beams through a table, 640 rows of 200 +
+        // 30: 18 with four, 24 with eight; 5 beams, no table, 320 rows of 900 +
+        // 10: 39 / 30).
+        const bool bm = beam_waves(n_bh, D, esize, k, (int)nt, t, table);
+        if (n_bh > kCus) {
+            if (D == 16 && (esize == 2 || bm || table)) return AttnPath::kWhole1;
+            if (table)
+                return k <= 3 && nt >= gen && tasks > kWaves && n_bh <= 2 * kCus ? AttnPath::kWhole2
+                                                                               : AttnPath::kWhole1;
+            if (k == 5 && nt <= 4 * kWaves) return AttnPath::kWhole1;
+        } else if (D == 16 && esize == 2 && k >= 3) {
+            return AttnPath::kWhole2;   // sixteen spill (192 rows of 300 + 300, 8 beams: 27 us against 16)
+        } else if (table && !bm && tasks > 2 * kWaves) {
+            // six beams' tasks and more spill in sixteen waves
+            if (D == 16) return AttnPath::kWhole2;
+            if (k >= 6 && n_bh < kSplitMaxRows && nt >= 4 * kWaves && gen <= nt) return AttnPath::kSplit;
+            if (k >= 6 && (n_bh >= kSplitMaxRows || tasks <= 4 * kWaves)) return AttnPath::kWhole2;
+        } else if (bm) {
+            // the generated tokens go to one workgroup of the split form, a
+            // beam or two per wave, beside the prefix's
+            if (n_bh < kSplitMaxRows && nt >= (k >= 6 ? 3 : 4) * kWaves &&
+                2 * nt >= 3 * ngt * ((k + kWaves - 1) / kWaves))
+                return AttnPath::kSplit;
+            if (k >= 6 && nt <= kWaves) return AttnPath::kWhole2;
+        }
+    }
     if (n_bh > kCus) {
         // More rows than CUs. Four waves where one round of four takes the row
         // (1024 rows of 16 generated tokens: 8.5 us against 10.0 with eight),
@@ -1651,7 +1873,7 @@ hipError_t launch_cross_attn(const void *q, const void *K, const void *V, const 
                              AttnPath path, const NgramRows *ngram)
 {
     AttnArgs a{q, K, V, src_len, out, B, k, H, S, D, nullptr, nullptr, 0, 0, nullptr, 0, workspace, epoch, stream,
-               NgramJob{nullptr, nullptr, 0, 0, 0, 0, 0, 0}, path};
+               NgramJob{nullptr, nullptr, 0, 0, 0, 0, 0, 0}, path, false};
     if (ngram)
         a.ng = NgramJob{ngram->tokens, ngram->logits, ngram->ld, ngram->t, ngram->n - 1, ngram->V, ngram->rows, 0};
     return bf16 ? launch_part<0>(a) : launch_part<1>(a);
@@ -1662,8 +1884,10 @@ hipError_t launch_prefix_attn(const void *q, const void *Kp, const void *Vp, con
                               void *out, int B, int k, int H, int N, int D, bool bf16, float *workspace,
                               unsigned long long epoch, hipStream_t stream, AttnPath path)
 {
+    const int esize = bf16 ? 2 : 4, tile = cross_attn_chunk_keys(D, esize) / kWaves;
     const AttnArgs a{q, Kp, Vp, prefix_len, out, B, k, H, N, D, Kt, Vt, T, t, anc, ld_anc, workspace, epoch, stream,
-                     NgramJob{nullptr, nullptr, 0, 0, 0, 0, 0, 0}, path};
+                     NgramJob{nullptr, nullptr, 0, 0, 0, 0, 0, 0}, path,
+                     beam_waves(B * H, D, esize, k, (N + tile - 1) / tile, t, anc != nullptr)};
     return bf16 ? launch_part<2>(a) : launch_part<3>(a);
 }
 #endif  // FS_ATTN_PART == 0

@@ -57,3 +57,23 @@ def test_encoder_decoder_bf16(k):
     for D in (32, 64, 128):   # sixteen waves have 128 each in any case: no scratch
         assert all(scratch == 0 for _, scratch in instances(D, True, k, False, 16)), D
     assert max(instances(32, True, k, False, 4))[0] <= 128
+
+
+@needs_tools
+@pytest.mark.parametrize("k", range(1, 9))
+def test_fp32(k):
+    for D in (32, 64, 128):
+        # without generated tokens: no scratch, four waves per SIMD in
+        # workgroups of eight (D = 64 and 32)
+        assert all(scratch == 0 for _, scratch in instances(D, False, k, False, 16)), D
+        if D < 128:
+            assert max(instances(D, False, k, False, 8)) <= (128, 0), D
+        # with them, not through a table: no scratch either, but for a few words
+        # of five beams at once (D = 32)
+        few = 40 if D == 32 and k in (4, 5) else 0
+        assert all(scratch <= few for _, scratch in instances(D, False, k, True, 16)), D
+        # through one, the walk of a beam per wave has none, and the tasks of up
+        # to four beams leave four waves per SIMD
+        assert min(scratch for _, scratch in instances(D, False, k, True, 16, table=True)) == 0, D
+        if k <= 4:
+            assert min(instances(D, False, k, True, 8, table=True)) <= (128, 0), D
