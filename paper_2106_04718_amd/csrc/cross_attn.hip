@@ -1253,7 +1253,6 @@ __device__ __forceinline__ void walk_row(RowLds<D, BF16, KB, KW, GEN, ANC, BM> &
             }
         };
         bool marked = !(ANC && ng > 0);
-        if constexpr (KB > 1) marked = marked || ngt == 1;   // the latest tile is never shared
         if constexpr (ANC) {
             // when the first round needs no more than the early tasks and
             // prefix tiles, the table is looked at after its loads have gone out
