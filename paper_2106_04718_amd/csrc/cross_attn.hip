@@ -1001,7 +1001,7 @@ __device__ __forceinline__ void generated_beams(RowLds<D, BF16, KB, KW, true, AN
                                                 const uint4 *__restrict__ q, int w, int gw, int b, int h, int H,
                                                 const GenRows &gr, float scale_log2)
 {
-    using TO = OwnTile<D, BF16, KB>;
+    using TO = OwnTile<D, BF16, 1>;   // of one query
     using G = Geo<D, BF16>;
     constexpr int kTile = G::kTile, kLpr = G::kLpr, kRpi = G::kRpi, kRow = kLpr * 16;
     const int lane = threadIdx.x & (kWave - 1);
@@ -1571,19 +1571,21 @@ __global__ __launch_bounds__(kBlock * P) void attn_whole_kernel(
 
 }  // namespace
 
-// Whether a wave walks a beam's generated tokens by itself (only where the
-// VALU tile attends them; the matrix-core tile's tasks spread over all waves).
-// Without a table every beam's rows are read in any case, and the loop of tasks
-// costs the registers of two tiles.  Through one, tasks read what the beams
-// share once, which pays from the second tile on; a beam's wave saves them the
-// look at the table (us, fp32, D = 64, k = 8, S = 300 keys, n rows, t tokens,
-// beams' waves against tasks: n = 256, t = 20: 19 / 23; n = 128, t = 150: 25 /
-// 25; n = 640, t = 500: 128 / 91).
+// Whether a wave walks a beam's generated tokens by itself.  Without a table
+// every beam's rows are read in any case.  On the vector tile the loop of tasks
+// costs the registers of two tiles then; on the matrix cores a wave per beam
+// saves the barrier and the fold that tasks take every KW tiles, which pays
+// from a few tiles on (us, bf16, D = 64, 8 beams, 144 rows of 0 + 300: beams
+// 18.3, tasks 22.6; D = 128, 4 beams: 18.9 and 23.4).  Through a table,
+// tasks read what the beams share once, which pays from the second tile on; on
+// the vector tile a beam's wave saves the look at the table (us, fp32, D = 64,
+// k = 8, 300 keys, n rows, t tokens, beams' waves / tasks: n = 256, t = 20 19 /
+// 23; n = 640, t = 500 128 / 91).
 inline bool beam_waves(int n_bh, int D, int esize, int k, int nt, int t, bool table) {
-    if (esize == 2 && D >= 32) return false;
+    const int tile = kIt * kWave * 16 / (D * esize);
+    if (esize == 2 && D >= 32) return !table && k >= 4 && t > tile * (k >= 6 ? 1 : 3);
     if (!table) return D == 16 ? k >= 3 : k == 4 || k >= 6;
     if (k < (D == 16 ? 3 : 4)) return false;
-    const int tile = kIt * kWave * 16 / (D * esize);
     const bool few = n_bh <= kCus || (nt == 0 && D > 16 && k >= 6);
     return t <= tile * (!few ? 1 : k >= 6 ? 3 : D == 16 && esize == 2 ? 2 : 1);
 }
@@ -1604,7 +1606,7 @@ struct AttnArgs {
     hipStream_t stream;
     NgramJob ng;          // n-gram rows of a fused decode step (ng.rows == 0: none)
     AttnPath path;        // decomposition chosen for the call
-    bool beams;           // generated tokens through a table by beam_waves
+    bool beams;           // generated tokens by beam_waves, where there are both kernels
 };
 
 namespace {
@@ -1680,7 +1682,12 @@ hipError_t launch_typed(const AttnArgs &a)
             }
             return launch_path<D, BF16, KB, true, true, false>(a);
         }
-        return launch_path<D, BF16, KB, true, false, kValu && (D == 16 ? KB >= 3 : KB == 4 || KB >= 6)>(a);
+        if constexpr (!kValu && KB >= 4) {
+            if (!a.beams) return launch_path<D, BF16, KB, true, false, false>(a);
+            return launch_path<D, BF16, KB, true, false, true>(a);
+        } else {
+            return launch_path<D, BF16, KB, true, false, kValu && (D == 16 ? KB >= 3 : KB == 4 || KB >= 6)>(a);
+        }
     } else {
         return launch_path<D, BF16, KB, false, false, false>(a);
     }
@@ -1787,6 +1794,12 @@ AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool 
     // The lines below were measured on MI355X over 16 to 1024 rows, 128 to 2048
     // keys, 0 to 500 generated tokens, D = 64 and 128, bf16 and f32 (graph
     // replays of three rotated inputs).
+    const bool bm = t > 0 && beam_waves(n_bh, D, esize, k, (int)nt, t, table);
+    // Beams' waves on the matrix cores spill in sixteen waves with D = 128 (us,
+    // bf16, 144 rows of 0 + 300, k = 4: 18.9 with eight, 26.2 with sixteen; D =
+    // 64, 48 rows of 200 + 300, k = 6: 14.9 and 13.6).
+    const bool split_gen = n_bh < kSplitMaxRows && nt >= 8 * kWaves && 2 * gen <= nt;   // as below
+    if (esize == 2 && D == 128 && bm && n_bh <= kCus && !split_gen) return AttnPath::kWhole2;
     if ((esize == 4 || D == 16) && t > 0) {
         // Generated tokens on the VALU tile (fp32, and D = 16).  More rows than
         // CUs: four waves where eight have more than 128 registers (one
@@ -1794,7 +1807,6 @@ AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool 
         // generated (us, fp32, D = 64, 4 beams through a table, 640 rows of 200 +
         // 30: 18 with four, 24 with eight; 5 beams, no table, 320 rows of 900 +
         // 10: 39 / 30).
-        const bool bm = beam_waves(n_bh, D, esize, k, (int)nt, t, table);
         if (n_bh > kCus) {
             if (D == 16 && (esize == 2 || bm || table)) return AttnPath::kWhole1;
             if (table)
@@ -1837,7 +1849,7 @@ AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool 
     // 2048 keys and 64 rows 18.4 against 30.4 us, but 300 more with 1024 keys
     // in bf16 19.3 against 16.9.
     if (n_bh < kSplitMaxRows) {
-        if (t > 0 ? nt >= 8 * kWaves && 2 * gen <= nt
+        if (t > 0 ? split_gen
                   : nt > 8 * kWaves || (nt > 4 * kWaves && n_bh > 16 && D < 128))
             return AttnPath::kSplit;
     }

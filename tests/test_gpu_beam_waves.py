@@ -1,9 +1,9 @@
-"""The split cache on the vector tile (fp32, and D = 16): beams attended in
-groups, and generated tokens walked a beam per wave or spread over all waves as
-tasks.  The two walks meet where the rule changes between them (one tile, three
-tiles); groups have remainders at odd beam counts.  Every decomposition gives
-the same bits, a beam's bits do not depend on how many beams there are, and all
-match the oracle.
+"""The split cache's two walks: generated tokens walked a beam per wave or
+spread over all waves as tasks; and beams attended in groups on the vector tile
+(fp32, and D = 16).  The two walks meet where the rule changes between them
+(one tile, three tiles); groups have remainders at odd beam counts.  Every
+decomposition gives the same bits, a beam's bits do not depend on how many
+beams there are, and all match the oracle.
 """
 import numpy as np
 import pytest
@@ -26,7 +26,8 @@ def draw(rng, dtype, *shape):
 
 
 # rows of a tile: 8 KiB of keys
-@pytest.mark.parametrize("dtype,D", [("f32", 16), ("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 16)])
+@pytest.mark.parametrize("dtype,D", [("f32", 16), ("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 16), ("bf16", 32),
+                                     ("bf16", 64), ("bf16", 128)])
 @pytest.mark.parametrize("k", [3, 4, 5, 6, 7, 8])
 def test_both_walks_at_their_edges(dtype, D, k):
     B, H, tile = 2, 2, 8192 // (D * (4 if dtype == "f32" else 2))
