@@ -40,6 +40,7 @@
 #include <atomic>
 
 
+#include "div.h"
 #include "launch.h"
 #include "trace.h"
 
@@ -61,21 +62,6 @@ constexpr int kWaves = kThreads / kWave;
 constexpr int kBlocks = kWave / kWaves;   // threshold blocks per wave: 64 in a workgroup
 constexpr int kSpan = kThreads * 4;       // window positions one load instruction of the workgroup covers
 constexpr int kGroupsMax = kPer / 4;      // 16-byte loads per thread at most
-
-// n / d for 0 <= n < 2^31 by a multiplication (d fixed on the host): mul =
-// floor(2^(31 + l) / d) + 1 with l = ceil(log2 d).
-struct Div {
-    unsigned mul;
-    int shift;
-    __device__ __forceinline__ unsigned operator()(unsigned n) const {
-        return (unsigned)(((unsigned long long)n * mul) >> shift);
-    }
-};
-inline Div make_div(int d) {
-    int l = 0;
-    while (l < 31 && (1ll << l) < d) ++l;
-    return Div{(unsigned)((1ull << (31 + l)) / (unsigned)d + 1), 31 + l};
-}
 
 // Maximum of three; fmaxf on loaded values first quiets them, one instruction
 // each (the logits are finite or -inf).

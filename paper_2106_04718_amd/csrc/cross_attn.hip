@@ -42,6 +42,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "div.h"
 #include "launch.h"
 #include "ngram_row.h"
 #include "trace.h"
@@ -271,23 +272,6 @@ __device__ __forceinline__ unsigned long long *trace_slot() {
 
 __device__ __forceinline__ int wave_id() {
     return __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-}
-
-// n / d for 0 <= n < 2^31 by a multiplication (d = 1 .. 2^31 - 1 fixed on the
-// host): mul = floor(2^(31 + l) / d) + 1 with l = ceil(log2 d), so that n * mul
-// exceeds n * 2^(31 + l) / d by at most n < 2^(31 + l) / d.  A division by a
-// kernel argument costs some 25 dependent instructions ahead of the first load.
-struct Div {
-    unsigned mul;
-    int shift;
-    __device__ __forceinline__ int operator()(int n) const {
-        return (int)(((unsigned long long)(unsigned)n * mul) >> shift);
-    }
-};
-inline Div make_div(int d) {
-    int l = 0;
-    while (l < 31 && (1ll << l) < d) ++l;
-    return Div{(unsigned)((1ull << (31 + l)) / (unsigned)d + 1), 31 + l};
 }
 
 // Merge softmax state (mb, lb, ab) into (m, l, a); m in the base-2 domain.
