@@ -284,7 +284,7 @@ union SelectLds {
 // logit v0 / 4) mod 4 positions before v0, so every load is 16 bytes whatever
 // V and the slice bounds are; window position w is slice position w - a.
 // Value j of a thread sits at window position lbase + offs(j), lbase = 4 *
-// thread: load g of the workgroup covers window positions [1024g, 1024g + 1024).
+// thread: load g of the workgroup covers window positions [kSpan*g, kSpan*(g + 1)).
 // Every 16-byte chunk the window reads holds at least one logit of the slice,
 // so no read leaves the pages of the logits.
 __device__ __forceinline__ constexpr int offs(int j) { return (j / 4) * kThreads * 4 + j % 4; }
@@ -572,7 +572,7 @@ __device__ __forceinline__ void select_slice(SliceLds &L, const float *__restric
             uint32_t last_hi = ~0u, last_lo = ~0u;
             for (int q = 0; q < c; ++q) {
                 // ~index of offset 0 (~(i + d) = ~i - d), opaque to the compiler in
-                // each round so that the 64 index halves are not kept across rounds
+                // each round so that the kVals index halves are not kept across rounds
                 uint32_t lo0 = ~(uint32_t)(v0 + lbase - a);
                 asm volatile("" : "+v"(lo0));
                 // (bh, bl) starts below every key whose high half is not 0, and

@@ -9,28 +9,33 @@
 // non-temporal 16-byte loads and keeps all k beams' work on that data in
 // registers.
 //
-// One launch, split-KV:
-//   One workgroup per (source b, head h, chunk c of C keys); 4 waves, each
-//   owning one tile of the chunk.  In a tile a group of kLpr lanes shares one
-//   row (16 bytes per lane), so a wave instruction reads kRpi whole rows.
-//     QK^T:  each lane dots its 16 bytes of the row with the same 16 bytes of
-//            every beam's query (held in registers); a butterfly inside the
-//            lane group completes the k scores.
-//     softmax: tile maximum and sum per beam by cross-group butterflies; the
-//            running (max, sum) of the online softmax is wave-uniform.
-//     PV:    the same lane layout reads V; each lane accumulates k x (its 16
-//            bytes of dims) in fp32.
-//   The waves' states are merged through LDS in a fixed order.  A source
-//   whose valid keys fit in one chunk is finished there.  Otherwise each
-//   chunk stores its partial (max, sum, unnormalised output) in the
-//   workspace and exits without waiting.
-//   One merger workgroup per (b, h), placed after all chunk workgroups in
-//   the grid (so dispatched after them), reads the chunks' records, merges
-//   them in chunk order, normalises and writes the output.  Each record word
-//   carries a tag of the call, so the merger knows when a record is
-//   complete; no fence or clearing of the workspace is needed.  The tag is
-//   the host's call epoch, or, for a call captured into a graph, a per-row
-//   counter in the workspace that the row's merger advances.
+// Tiles.  A wave attends one tile of 4096 / D keys for all k beams; kWaves
+// tiles make a chunk.  A group of kLpr lanes shares a row (16 bytes per lane),
+// so a wave instruction reads kRpi whole rows.
+//   bf16, D >= 32 (MfmaTile): the K rows go through LDS to the A operand of
+//     v_mfma_f32_16x16x32_bf16, the beams' queries are its columns; a lane then
+//     holds 16 scores of one beam.  V is read back transposed for PV.
+//   fp32, and D = 16 (ValuTile): each lane dots its 16 bytes of the row with
+//     the same 16 bytes of the beams' queries, a reduce-scatter in the lane
+//     group completes the scores, and PV accumulates in fp32 in the row layout.
+//     Many beams go a group at a time, so that their sums stay in registers.
+//   Both keep a tile's state as (maximum, sum, unnormalised output) per beam.
+// Decompositions, one launch each, chosen by choose_attn_path:
+//   attn_whole_kernel: one workgroup of 4, 8 or 16 waves per (b, h), which
+//     walks the row's tile tasks one per wave and round (walk_row) and folds
+//     each round's states into the row's.  No workspace.
+//   cross_attn_kernel (split-KV, few long rows): one workgroup per chunk.  Rows
+//     of more than one chunk store one record per chunk in the workspace, and a
+//     merger workgroup per (b, h), after all chunk workgroups in the grid (so
+//     dispatched after them), folds them in chunk order.  Each record word
+//     carries a tag of the call, so the merger knows when a record is
+//     complete; no fence or clearing of the workspace is needed.  The tag is
+//     the host's call epoch, or, for a call captured into a graph, a per-row
+//     counter in the workspace that the row's merger advances.
+// Generated tokens of a split cache are the same tiles: tasks of the walk, or,
+// where beam_waves says so, a beam per wave before it (generated_beams).
+// Every form folds the same states in the same order (the chunks of the prefix,
+// then each beam's generated tiles), so all give the same bits.
 // Rows j >= src_len[b] are never read.  The chunk size depends only on the
 // row size, and each beam's arithmetic is the same whatever k is, so the
 // output bits do not depend on k, B or the beam's position.
@@ -1772,9 +1777,9 @@ AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool 
     const long long nt = (S + tile - 1) / tile, ngt = (t + tile - 1) / tile;
     const long long gen = ngt == 0 ? 0 : table ? ngt - 1 + k : ngt * k;
     const long long tasks = nt + gen;
-    // The kernels that read through a table with D = 128 or in fp32 have more
-    // than 128 registers: three waves per SIMD.
-    const bool heavy = table && t > 0 && (D >= 128 || esize == 4);
+    // In bf16 the kernels that read through a table with D = 128 have more than
+    // 128 registers (130 to 208): three or two waves per SIMD.
+    const bool heavy = table && t > 0 && D >= 128 && esize == 2;
     // The lines below were measured on MI355X over 16 to 1024 rows, 128 to 2048
     // keys, 0 to 500 generated tokens, D = 64 and 128, bf16 and f32 (graph
     // replays of three rotated inputs).
@@ -1817,8 +1822,7 @@ AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool 
         // More rows than CUs. Four waves where one round of four takes the row
         // (1024 rows of 16 generated tokens: 8.5 us against 10.0 with eight),
         // eight otherwise (768 rows of 512 keys: 12.6 against 13.5). Of three
-        // waves per SIMD, workgroups of eight leave a third unused (f32, 512
-        // rows, 500 tokens: 29.7 us with four against 40.4).
+        // waves per SIMD, workgroups of eight leave a third unused.
         return tasks <= kWaves || heavy ? AttnPath::kWhole1 : AttnPath::kWhole2;
     }
     // A CU for every row: as many waves as the row has tasks, so that all of
@@ -1839,7 +1843,7 @@ AttnPath choose_attn_path(int n_bh, int S, int D, int esize, int k, int t, bool 
     }
     // Sixteen waves with D = 128 and a table spill: 256 rows of 256 + 64 rows
     // 14.8 us against 10.9 with eight.
-    return heavy && esize == 2 ? AttnPath::kWhole2 : AttnPath::kWhole4;
+    return heavy ? AttnPath::kWhole2 : AttnPath::kWhole4;
 }
 
 bool may_split(int n_bh, int S, int D, int esize) {
@@ -1854,8 +1858,9 @@ int cross_attn_chunk_keys(int D, int esize) {
 
 size_t cross_attn_workspace_floats(int B, int k, int H, int S, int D, int esize, bool split) {
     const int C = cross_attn_chunk_keys(D, esize);
-    // one record per tile of the row (kWaves tiles per chunk), plus the
-    // generated-token record of the split cache
+    // Records are one per chunk, and one for the generated tokens of the split
+    // cache; kWaves slots per chunk are asked for, so that what callers have
+    // sized, and what fs_beam_decode_step_noalloc refuses, stays as it was.
     const size_t NT = (size_t)std::max(1, (S + C - 1) / C) * kWaves + (split ? 1 : 0);
     const size_t n_bh = (size_t)B * H;
     const size_t part = n_bh * NT * (size_t)k * (size_t)(D + 2);

@@ -47,9 +47,9 @@ hipError_t set_select_trace(unsigned long long *buf, unsigned int cap);
 AttnPath set_attn_path_override(AttnPath p);
 int set_select_slices_override(int slices);
 
-// Workspace size in 4-byte words: the per-tile partial records (plus one
-// record per (b, h) for the generated-token segment when `split`), then one
-// 64-bit counter per (b, h) for captured calls.
+// Workspace size in 4-byte words: the partial records (one per chunk, in a
+// quarter of the slots asked for, plus one per (b, h) for the generated-token
+// segment when `split`), then one 64-bit counter per (b, h) for captured calls.
 size_t cross_attn_workspace_floats(int B, int k, int H, int S, int D, int esize, bool split);
 
 // The n-gram part of a fused decode step (the arguments of fs_ngram_block):
