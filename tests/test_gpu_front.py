@@ -122,3 +122,36 @@ def test_native_checks_take_and_refuse_what_the_general_path_does(call, monkeypa
             assert a == b, (call, name)
         else:
             assert a == b, (call, name)
+
+
+class Spy:
+    """The native module, with what each call returned."""
+
+    def __init__(self, native):
+        self.native, self.seen = native, []
+
+    def __getattr__(self, name):
+        def call(*a):
+            r = getattr(self.native, name)(*a)
+            self.seen.append(r)
+            return r
+        return call
+
+
+# forms that the native module leaves to the general path, by call
+DECLINED = {
+    "cross": ["q strided", "sealed"], "step": ["t numpy", "q strided", "tok cpu", "tok columns", "sealed"],
+    "prefix": ["t numpy", "q strided", "sealed"], "table": ["t numpy", "q strided", "sealed"],
+    "ngram": ["t numpy", "tok cpu", "tok columns", "sealed"], "select": ["t numpy", "tok cpu", "tok columns", "sealed"],
+    "reorder": ["t numpy", "k numpy", "sealed"], "ancestry": ["t numpy", "k numpy", "sealed"],
+}
+
+
+@pytest.mark.parametrize("call", CALLS)
+def test_the_native_module_takes_the_plain_call_and_leaves_the_others(call, monkeypatch):
+    for name in ["plain", *DECLINED[call]]:
+        say(f"[front] {call}: {name}")
+        spy = Spy(api._load_fast())
+        monkeypatch.setattr(api, "_fast", spy)
+        outcome(call, CHANGES[name])
+        assert spy.seen == [0 if name == "plain" else None], name
